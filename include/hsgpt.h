@@ -113,7 +113,10 @@ typedef struct hsg_ensemble {
 
 /* Tuning knobs of the sweep kernels (0 = library default). */
 typedef struct hsg_tuning {
-    int32_t path;           /* 0 auto (3 if a replica fits in one workgroup's LDS, else 2);
+    int32_t path;           /* 0 auto: the register-resident kernel where it is the faster
+                               one (binary32 L = 18 .. 26, binary64 L = 16 and 18; not with
+                               block_threads or replicas_per_block set), else 3 if a replica
+                               fits in one workgroup's LDS, else 2;
                                1 LDS-resident lattice on persistent double-buffered
                                workgroups; 2 streaming half-sweeps; 3 LDS-resident lattice,
                                one workgroup per replica; 4 wavefront: one workgroup per
@@ -269,8 +272,7 @@ hsg_status hsg_measure(const hsg_ensemble* ens, int n_ens, void* stream);
  * chains' replicas of a temperature and measures them from LDS (measured faster
  * there); binary32 ones at L = 16 take one launch in which a workgroup sweeps the two
  * replicas of a temperature in turn, the couplings loaded once, and then measures
- * them.  On the streaming path (lattices whose replica does not fit one workgroup's
- * LDS) the measurement also adds up the last sweep's per-tile energies, in place of
+ * them.  On the streaming path the measurement also adds up the last sweep's per-tile energies, in place of
  * the sweep's own finishing launch, in the same order (energies and counters bit for
  * bit those of hsg_sweep).  Other ensembles take the two calls.  Needs what both
  * calls need; n_sweeps = 0 measures only. */

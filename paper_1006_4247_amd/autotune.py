@@ -1,6 +1,6 @@
 """Autotuner for the sweep kernels.
 
-For an ensemble shape it times every supported kernel variant (LDS-resident with
+For an ensemble shape it times every supported kernel variant (the default, LDS-resident with
 one workgroup per replica at several block sizes, persistent double-buffered
 workgroups, streaming half-sweeps at several block sizes and replicas per
 workgroup) on a throwaway ensemble of the same shape (the caller's Markov chains
@@ -17,7 +17,8 @@ from . import _abi
 from .ensemble import Ensemble, geometric_betas
 
 CANDIDATES = (
-    [{"path": 3, "block_threads": nt} for nt in (0, 256, 512)]
+    [{"path": 0}]  # the library's default
+    + [{"path": 3, "block_threads": nt} for nt in (0, 256, 512)]
     + [{"path": 1, "block_threads": 0}]
     + [{"path": 6, "block_threads": 0}]
     + [{"path": 4, "block_threads": 0}]
@@ -33,7 +34,7 @@ def _cache_path():
 
 def _key(L, S, C, R, precision, n_hb, n_or, device):
     name = torch.cuda.get_device_properties(device).name.replace(" ", "_")
-    return "%s/L%d/S%d/C%d/R%d/%s/%d+%d" % (name, L, S, C, R, precision, n_hb, n_or)
+    return "2/%s/L%d/S%d/C%d/R%d/%s/%d+%d" % (name, L, S, C, R, precision, n_hb, n_or)
 
 
 def _time(ens, tuning, n_hb, n_or, reps):

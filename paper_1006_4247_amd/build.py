@@ -14,7 +14,7 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 LIB = os.path.join(HERE, "libhsgpt.so")
 BUILD_DIR = os.path.join(HERE, "_build")
-SOURCES = ["abi.hip", "sweep_resident.hip", "sweep_stream.hip", "sweep_wave.hip", "exchange.hip",
+SOURCES = ["abi.hip", "sweep_resident.hip", "sweep_column.hip", "sweep_stream.hip", "sweep_wave.hip", "exchange.hip",
            "decimate.hip", "coolheat.hip", "mlp.hip", "plan.hip", "sweep_batch.hip", "probe.hip"]
 ARCH = os.environ.get("HSG_OFFLOAD_ARCH", "gfx950")
 

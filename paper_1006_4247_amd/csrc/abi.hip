@@ -93,17 +93,25 @@ hipStream_t as_stream(void* s) { return static_cast<hipStream_t>(s); }
 
 // 1: LDS-resident, persistent double-buffered; 3: LDS-resident, one workgroup per
 // replica; 2: streaming half-sweeps; 4: wavefront over z-planes; 6: LDS-resident,
-// persistent single-buffer; 0: 3 if a replica fits in LDS, else 2 (measured faster
-// than 4 at L = 20 .. 40).
-int sweep_path(const hsg_ensemble& e, const hsg_tuning* t) {
+// persistent single-buffer; 0: the register-resident kernel (kColumn here) where it is
+// the faster one for the call and no launch shape is asked for, else 3 if a replica fits
+// in LDS, else 2.
+constexpr int kColumn = 100;
+int sweep_path(const hsg_ensemble& e, const hsg_tuning* t, int n_sweeps, int n_hb, int n_or) {
     const int path = t ? t->path : 0;
     if (path != 0) return path;
+    const bool shaped = t && (t->block_threads != 0 || t->replicas_per_block != 0);
+    if (!shaped && hsg::column_faster(e, n_sweeps, n_hb, n_or)) return kColumn;
     if (hsg::resident_supported(e)) return 3;
     return 2;
 }
 
-// Every path but the streaming one works without the scratch.
-bool use_resident(const hsg_ensemble& e, const hsg_tuning* t) { return sweep_path(e, t) != 2; }
+// Calls whose descriptor must carry the scratch: those on the streaming path, and by
+// default every lattice beyond one workgroup's LDS, whichever kernel then sweeps it.
+bool needs_scratch(const hsg_ensemble& e, const hsg_tuning* t) {
+    const int path = t ? t->path : 0;
+    return path == 2 || (path == 0 && !hsg::resident_supported(e));
+}
 
 // The library's own copy of a descriptor for the sweep kernels, its internal flag
 // word set from the tuning (renormalisation of sweeps without heat-bath on unless
@@ -188,7 +196,7 @@ hsg_status hsg_sweep_tuned(const hsg_ensemble* ens, int n_ens, int n_sweeps, int
         if (tuning && tuning->path == 6 && !hsg::chain_supported(ens[i]))
             return fail(HSG_ERR_UNSUPPORTED,
                         "ensemble %d: the persistent single-buffer path takes binary32 at L = 16", i);
-        if (!use_resident(ens[i], tuning)) {
+        if (needs_scratch(ens[i], tuning)) {
             s = check_one(ens[i], i, kScratch);
             if (s != HSG_OK) return s;
         }
@@ -197,9 +205,11 @@ hsg_status hsg_sweep_tuned(const hsg_ensemble* ens, int n_ens, int n_sweeps, int
     for (int i = 0; i < n_ens; ++i) {
         const int nt = tuning ? tuning->block_threads : 0;
         hipError_t err;
-        const int path = sweep_path(ens[i], tuning);
+        const int path = sweep_path(ens[i], tuning, n_sweeps, n_hb, n_or);
         const hsg_ensemble e = launch_copy(ens[i], tuning);
-        if (path == 1) {
+        if (path == kColumn) {
+            err = hsg::launch_column_sweeps(e, n_sweeps, n_hb, n_or, as_stream(stream));
+        } else if (path == 1) {
             err = hsg::launch_resident(e, n_sweeps, n_hb, n_or, 2, 0, nt, as_stream(stream));
         } else if (path == 3) {
             err = hsg::launch_resident(e, n_sweeps, n_hb, n_or, 0, 0, nt, as_stream(stream));
@@ -233,7 +243,7 @@ hsg_status hsg_sweep_static(const hsg_ensemble* ens, int n_ens, int n_sweeps, in
     if (s != HSG_OK) return s;
     bool any_stream = false;
     for (int i = 0; i < n_ens; ++i) {
-        if (use_resident(ens[i], nullptr)) continue;
+        if (!needs_scratch(ens[i], nullptr)) continue;
         any_stream = true;
         const hsg::ScratchLayout sl = hsg::scratch_layout(ens[i]);
         const size_t need = static_cast<size_t>(ens[i].n_samples) * ens[i].n_chains * ens[i].n_temps * sl.max_tiles;
@@ -252,7 +262,10 @@ hsg_status hsg_sweep_static(const hsg_ensemble* ens, int n_ens, int n_sweeps, in
     for (int i = 0; i < n_ens; ++i) {
         hipError_t err;
         const hsg_ensemble e = launch_copy(ens[i]);
-        if (use_resident(e, nullptr))
+        const int path = sweep_path(e, nullptr, n_sweeps, n_hb, n_or);
+        if (path == kColumn)
+            err = hsg::launch_column_sweeps(e, n_sweeps, n_hb, n_or, as_stream(stream));
+        else if (path == 3)
             err = hsg::launch_resident(e, n_sweeps, n_hb, n_or, 0, 0, 0, as_stream(stream));
         else
             err = hsg::launch_stream_sweeps(e, n_sweeps, n_hb, n_or, 0, 0, partial, as_stream(stream));
@@ -297,7 +310,9 @@ hsg_status hsg_anneal_swap(const hsg_ensemble* ens, int n_ens, int parity, int n
     for (int i = 0; i < n_ens; ++i) {
         hipError_t err;
         const hsg_ensemble e = launch_copy(ens[i]);
-        if (hsg::resident_supported(e))
+        if (hsg::column_supported(e) && e.L > 16)
+            err = hsg::launch_column_legs(e, parity, n_hb, n_or, as_stream(stream));
+        else if (hsg::resident_supported(e))
             err = hsg::launch_resident(e, 0, n_hb, n_or, 1, parity, 0, as_stream(stream));
         else
             err = hsg::launch_stream_anneal(e, parity, n_hb, n_or, 0, as_stream(stream));
@@ -377,7 +392,7 @@ hsg_status hsg_sweep_measure(const hsg_ensemble* ens, int n_ens, int n_sweeps, i
     hsg_status s = check_all(ens, n_ens, kState | kMeasure);
     if (s != HSG_OK) return s;
     for (int i = 0; i < n_ens; ++i) {
-        if (!use_resident(ens[i], nullptr)) {
+        if (needs_scratch(ens[i], nullptr)) {
             s = check_one(ens[i], i, kScratch);
             if (s != HSG_OK) return s;
         }
@@ -394,7 +409,7 @@ hsg_status hsg_sweep_measure(const hsg_ensemble* ens, int n_ens, int n_sweeps, i
             if (err != hipSuccess) return device(err, "sweep and measure");
             continue;
         }
-        if (n_sweeps > 0 && !use_resident(ens[i], nullptr)) {
+        if (n_sweeps > 0 && sweep_path(ens[i], nullptr, n_sweeps, n_hb, n_or) == 2) {
             // streaming sweeps: the measurement adds up the last sweep's per-tile
             // energies itself, in place of the sweep's own finishing pass
             int n_tiles = 0;

@@ -252,6 +252,19 @@ __device__ __forceinline__ void overrelax(T sx, T sy, T sz, T Sx, T Sy, T Sz, T&
     }
 }
 
+// The same reflection without a branch (the same bits), for kernels that update several
+// independent sites as one block.
+template <typename T>
+__device__ __forceinline__ void overrelax_flat(T sx, T sy, T sz, T Sx, T Sy, T Sz, T& ox, T& oy,
+                                               T& oz) {
+    const T ss = fma(Sz, Sz, fma(Sy, Sy, Sx * Sx));
+    const T f = T(2) * fma(sz, Sz, fma(sy, Sy, sx * Sx)) * d_rcp(ss);
+    const bool refl = ss > T(0);
+    ox = refl ? fma(f, Sx, -sx) : sx;
+    oy = refl ? fma(f, Sy, -sy) : sy;
+    oz = refl ? fma(f, Sz, -sz) : sz;
+}
+
 // Binary32 spins leave the unit sphere slowly under reflections alone (each one rounds;
 // a heat-bath update writes a fresh unit vector), so sweeps without a heat-bath lattice
 // sweep renormalise every spin once per sweep, in their last overrelaxation lattice

@@ -57,6 +57,13 @@ bool resident_mseq_supported(const hsg_ensemble& e);
 hipError_t launch_resident_mseq(const hsg_ensemble& e, int n_sweeps, int n_hb, int n_or, hipStream_t st);
 hipError_t launch_resident_pair(const hsg_ensemble& e, int n_sweeps, int n_hb, int n_or, hipStream_t st);
 
+// Register-resident sweeps and annealing legs (sweep_column.hip): one workgroup per
+// replica (or leg), whose spins stay in its threads' registers for the whole call.
+bool column_supported(const hsg_ensemble& e);
+bool column_faster(const hsg_ensemble& e, int n_sweeps, int n_hb, int n_or);  // ... and the better kernel for the call
+hipError_t launch_column_sweeps(const hsg_ensemble& e, int n_sweeps, int n_hb, int n_or, hipStream_t st);
+hipError_t launch_column_legs(const hsg_ensemble& e, int parity, int n_hb, int n_or, hipStream_t st);
+
 // Wavefront path: one workgroup per replica walking its z-planes, one HBM pass per
 // lattice sweep (L = 18 .. 40 in binary32, .. 28 in binary64, LDS permitting); a
 // tuning option, slower than the streaming path where measured.

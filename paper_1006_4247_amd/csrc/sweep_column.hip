@@ -1,0 +1,515 @@
+// Register-resident sweeps for lattices around and beyond one workgroup's LDS: binary32
+// L = 18 .. 26, binary64 L = 16 and 18.
+//
+// One workgroup owns one replica for the whole call.  Thread (g, q) owns the sites of both
+// sublattices at place q = ih + (L/2) j of the planes z = g ZP .. g ZP + ZP - 1: their spins
+// stay in its registers, so two of a site's neighbours along z are its own (other
+// sublattice, same place, planes z - 1 and z + 1) and only those in the plane, and the
+// ones beyond its run of planes, come from LDS.  LDS holds one sublattice at a time, the
+// one the current half-sweep reads: a half-sweep reads it, waits, and writes the updated
+// sublattice over it.  HBM sees one read and one write of the replica per call, however
+// many sweeps it makes, where the streaming kernels move three half-replicas per
+// half-sweep.  The couplings along z stay in registers too; the other four of a site come
+// from the L2 in every half-sweep, asked for two sites ahead.  Binary32 heat-bath
+// half-sweeps draw the uniforms first, one Philox block per site pair, into LDS (where it
+// has room for them).
+//
+// What bounds it (L = 24, 8 x 2 x 16 replicas, one per CU): an overrelaxation half-sweep
+// takes 2.9 us, in which the VALU is 51 % and the LDS 47 % busy, the two only partly
+// overlapping between the barriers of the one workgroup a CU holds.  1 heat-bath + 30
+// overrelaxation lattice sweeps of 8 x 2 x 27 replicas: 0.46 ms, against 1.42 ms in 62
+// streaming launches at the rate of HBM.
+//
+// Spins are those of the other sweep kernels bit for bit (same site arithmetic, order of
+// the field's terms and random numbers).
+#include "hsg_device.h"
+#include "hsg_launch.h"
+
+#include <type_traits>
+
+namespace hsg {
+
+// ZP planes per run; WPE waves per SIMD the registers are budgeted for; SEL: the neighbour
+// along x that is the thread's own is taken from its registers (two selects per component)
+// instead of LDS; FENCE: bits 1, 2, 4 keep the compiler from mixing a site's loads with its
+// arithmetic, a site with the next, two sites with the next two (measured per size).
+template <typename T, int L>
+struct ColumnShape;
+template <int ZP_, int WPE_, bool SEL_, int FENCE_>
+struct ColumnTuning {
+    static constexpr int ZP = ZP_, WPE = WPE_, FENCE = FENCE_;
+    static constexpr bool SEL = SEL_;
+};
+template <> struct ColumnShape<float, 18> : ColumnTuning<6, 4, true, 4> {};   // two workgroups per CU
+template <> struct ColumnShape<float, 20> : ColumnTuning<4, 4, true, 4> {};
+template <> struct ColumnShape<float, 22> : ColumnTuning<11, 2, false, 3> {};
+template <> struct ColumnShape<float, 24> : ColumnTuning<8, 4, false, 3> {};
+template <> struct ColumnShape<float, 26> : ColumnTuning<13, 3, false, 3> {};
+template <> struct ColumnShape<double, 16> : ColumnTuning<4, 2, false, 2> {};
+template <> struct ColumnShape<double, 18> : ColumnTuning<6, 2, false, 3> {};
+
+template <typename T, int L>
+struct Column : ColumnShape<T, L> {
+    static constexpr int ZP = ColumnShape<T, L>::ZP;
+    static constexpr int HL = L / 2, PL = HL * L, NH = PL * L, N = 2 * NH, NQ = NH / 2;
+    static constexpr int ZG = L / ZP;                      // runs of planes
+    static constexpr int NT = ((PL * ZG + 63) / 64) * 64;  // threads
+    static constexpr int B = static_cast<int>(sizeof(T));
+    // LDS: one sublattice [3][NH], and the heat-bath uniforms [2][NH] of a half-sweep
+    static constexpr bool DRAWN = sizeof(T) == 4 && 5 * NH * 4 <= 150 * 1024;
+    static constexpr size_t LDS = static_cast<size_t>(DRAWN ? 5 : 3) * NH * sizeof(T);
+    static_assert(L % ZP == 0 && ZP >= 2 && NT <= 1024, "one workgroup");
+};
+
+__device__ __forceinline__ float buffer_get(__amdgpu_buffer_rsrc_t r, int voff, int soff, float) {
+    return __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, voff, soff, 0));
+}
+__device__ __forceinline__ double buffer_get(__amdgpu_buffer_rsrc_t r, int voff, int soff, double) {
+    typedef unsigned int u2 __attribute__((ext_vector_type(2)));
+    const u2 v = __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, 0);
+    return __hiloint2double(static_cast<int>(v.y), static_cast<int>(v.x));
+}
+
+// What a thread keeps for the whole call.
+template <typename T, int L>
+struct ColumnState {
+    static constexpr int ZP = Column<T, L>::ZP;
+    T s[2][ZP][3];    // spins [sublattice][plane of the run][component]
+    T jb[2][4];       // couplings in the plane of the next two sites to update
+    T jz[2][ZP + 1];  // bonds along z: [sublattice of the lower end][plane - first plane + 1]
+    // byte offsets of sites in a sublattice's array, in LDS and of the couplings alike: own
+    // site of the run's first plane; [(P + m) & 1][+x, -x] (SEL: [..][2] is the one that is
+    // not the thread's own); y neighbours; the planes below and above the run
+    int own, x[2][3], yp, ym, zm, zp;
+    bool on, o0;  // a thread with sites; x = 2 ih + o with o = o0 where (P + m) is even
+    __amdgpu_buffer_rsrc_t J;
+    uint32_t g;
+    int k0, k1;
+};
+
+// The couplings in the plane of the site of sublattice P in plane m of the run.
+template <typename T, int L, int P>
+__device__ __forceinline__ void column_bonds(const ColumnState<T, L>& c, T (&j)[4], int m, int so) {
+    using M = Column<T, L>;
+    constexpr int PL = M::PL, NH = M::NH, Q = 1 - P, B = M::B;
+    j[0] = buffer_get(c.J, c.own, so + (P * NH + m * PL) * B, T());
+    j[1] = buffer_get(c.J, c.x[(P + m) & 1][1], so + (Q * NH + m * PL) * B, T());
+    j[2] = buffer_get(c.J, c.own, so + ((2 + P) * NH + m * PL) * B, T());
+    j[3] = buffer_get(c.J, c.ym, so + ((2 + Q) * NH + m * PL) * B, T());
+}
+
+// One half-sweep of sublattice P: KIND 1 heat-bath, 2 overrelaxation, 3 overrelaxation
+// with the energy, 0 general (kind, renormalisation and energy from the arguments).
+template <typename T, int L, int P, int KIND>
+__device__ __forceinline__ void column_half(ColumnState<T, L>& c, T* __restrict__ lds, bool hb_arg, bool rn_arg,
+                                            bool want_arg, int hs, T beta, uint32_t tsw, double& acc, bool& bad) {
+    using M = Column<T, L>;
+    constexpr int PL = M::PL, NH = M::NH, NQ = M::NQ, ZP = M::ZP, NT = M::NT, Q = 1 - P;
+    const bool hb = KIND == 0 ? hb_arg : KIND == 1;
+    const bool rn = KIND == 0 && rn_arg;
+    const bool want = KIND == 3 || (KIND == 0 && want_arg);
+    // opaque copies keep the couplings' scalar offsets and the generator's key schedule inside
+    // the half-sweep instead of letting them be hoisted and held in registers across the
+    // kernel (no instruction emitted)
+    int so = 0, k0 = __builtin_amdgcn_readfirstlane(c.k0), k1 = __builtin_amdgcn_readfirstlane(c.k1);
+    asm volatile("" : "+s"(so), "+s"(k0), "+s"(k1));
+    const auto at = [&](int off, int el) -> T& {  // LDS: byte offset of a thread + constant element
+        return *reinterpret_cast<T*>(reinterpret_cast<unsigned char*>(lds) + off + el * M::B);
+    };
+    T* rnd = lds + 3 * NH;
+    if (M::DRAWN && hb) {  // one Philox block per site pair (h, h + N/4)
+        for (int h = static_cast<int>(threadIdx.x); h < NQ; h += NT) {
+            const Words w = philox(static_cast<uint32_t>(h), tsw, c.g, heatbath_c3(hs), static_cast<uint32_t>(k0),
+                                   static_cast<uint32_t>(k1));
+            rnd[h] = static_cast<T>(u01_23(w.w0));
+            rnd[NH + h] = static_cast<T>(u01_23(w.w1));
+            rnd[NQ + h] = static_cast<T>(u01_23(w.w2));
+            rnd[NH + NQ + h] = static_cast<T>(u01_23(w.w3));
+        }
+        lds_barrier();
+    }
+#pragma unroll
+    for (int m = 0; m < ZP; ++m) {
+        const int e = (P + m) & 1;
+        T j[4];
+#pragma unroll
+        for (int d = 0; d < 4; ++d) j[d] = c.jb[m & 1][d];
+        T n[4][3], zlo[3], zhi[3];
+#pragma unroll
+        for (int mu = 0; mu < 3; ++mu) {
+            const int pl = mu * NH + m * PL;
+            if constexpr (M::SEL) {
+                const T far = at(c.x[e][2], pl), near = c.s[Q][m][mu];
+                const bool o = e ? !c.o0 : c.o0;
+                n[0][mu] = o ? far : near;
+                n[1][mu] = o ? near : far;
+            } else {
+                n[0][mu] = at(c.x[e][0], pl);
+                n[1][mu] = at(c.x[e][1], pl);
+            }
+            n[2][mu] = at(c.yp, pl);
+            n[3][mu] = at(c.ym, pl);
+            zlo[mu] = m > 0 ? c.s[Q][m > 0 ? m - 1 : 0][mu] : at(c.zm, mu * NH);
+            zhi[mu] = m + 1 < ZP ? c.s[Q][m + 1 < ZP ? m + 1 : 0][mu] : at(c.zp, mu * NH);
+        }
+        // the couplings of the site after next
+        if (m + 2 < ZP) column_bonds<T, L, P>(c, c.jb[m & 1], m + 2, so);
+        if (M::FENCE & 1) __builtin_amdgcn_sched_barrier(0);
+        T S[3];
+#pragma unroll
+        for (int mu = 0; mu < 3; ++mu) {
+            T v = T(0);
+#pragma unroll
+            for (int d = 0; d < 4; ++d) v = fma(j[d], n[d][mu], v);
+            v = fma(c.jz[P][m + 1], zhi[mu], v);
+            v = fma(c.jz[Q][m], zlo[mu], v);
+            S[mu] = v;
+        }
+        T ox, oy, oz;
+        if (hb) {
+            T r1, r2;
+            int h = c.own / M::B + m * PL;
+            if (!M::DRAWN) asm volatile("" : "+v"(h));  // the generator's first round stays in the half-sweep too
+            if constexpr (M::DRAWN) {
+                r1 = at(c.own, 3 * NH + m * PL);
+                r2 = at(c.own, 4 * NH + m * PL);
+            } else if constexpr (sizeof(T) == 4) {
+                const bool hi = h >= NQ;
+                const Words w = philox(static_cast<uint32_t>(hi ? h - NQ : h), tsw, c.g, heatbath_c3(hs),
+                                       static_cast<uint32_t>(k0), static_cast<uint32_t>(k1));
+                r1 = static_cast<T>(u01_23(hi ? w.w2 : w.w0));
+                r2 = static_cast<T>(u01_23(hi ? w.w3 : w.w1));
+            } else {
+                const Words w = philox(static_cast<uint32_t>(h), tsw, c.g, heatbath_c3(hs), static_cast<uint32_t>(k0),
+                                       static_cast<uint32_t>(k1));
+                r1 = static_cast<T>(u01_52(w.w0, w.w1));
+                r2 = static_cast<T>(u01_52(w.w2, w.w3));
+            }
+            heatbath<T>(S[0], S[1], S[2], beta, r1, r2, ox, oy, oz);
+        } else {
+            overrelax_flat<T>(c.s[P][m][0], c.s[P][m][1], c.s[P][m][2], S[0], S[1], S[2], ox, oy, oz);
+            if (rn) renormalize(ox, oy, oz);
+        }
+        c.s[P][m][0] = ox;
+        c.s[P][m][1] = oy;
+        c.s[P][m][2] = oz;
+        if (want && c.on) {
+            const double dx = ox, dy = oy, dz = oz;
+            acc += fma(dz, static_cast<double>(S[2]), fma(dy, static_cast<double>(S[1]), dx * static_cast<double>(S[0])));
+            const double n2 = fma(dz, dz, fma(dy, dy, dx * dx));
+            if (!(fabs(n2 - 1.0) <= NormTol<T>::value)) bad = true;
+        }
+        if ((M::FENCE & 2) || ((M::FENCE & 4) && (m & 1))) __builtin_amdgcn_sched_barrier(0);
+    }
+    // the couplings of the next half-sweep's first two sites
+    column_bonds<T, L, Q>(c, c.jb[0], 0, so);
+    column_bonds<T, L, Q>(c, c.jb[1], 1, so);
+    lds_barrier();  // every thread has read the other sublattice
+    if (c.on) {
+#pragma unroll
+        for (int m = 0; m < ZP; ++m)
+#pragma unroll
+            for (int mu = 0; mu < 3; ++mu) at(c.own, mu * NH + m * PL) = c.s[P][m][mu];
+    }
+    lds_barrier();
+}
+
+// One sweep: n_hb heat-bath then n_or overrelaxation lattice sweeps, sublattice 0 before 1,
+// or (ADJ) in reverse.  The loops over kinds are separate so that the spins a thread holds
+// stay in place from one half-sweep to the next.
+template <typename T, int L, bool ADJ>
+__device__ __forceinline__ void column_sweep(ColumnState<T, L>& c, T* __restrict__ lds, int n_hb, int n_or, bool renorm,
+                                             bool want, T beta, uint32_t tsw, double& acc, bool& bad) {
+    constexpr int P0 = ADJ ? 1 : 0, P1 = 1 - P0;
+    const int n_lat = n_hb + n_or;
+    // the lattice sweep that renormalises (the last overrelaxation one of the forward order,
+    // where there is no heat-bath) or ends with the energy runs in the general form
+    const int head = ADJ && renorm ? 1 : 0, tail = (want || (renorm && !ADJ)) && !(head && n_lat == 1) ? 1 : 0;
+    const auto general = [&](int i) {  // i-th lattice sweep of the call's order
+        const int l = ADJ ? n_lat - 1 - i : i;
+        const bool hb = l < n_hb, rn = renorm && l == n_lat - 1, w = want && i == n_lat - 1;
+        column_half<T, L, P0, 0>(c, lds, hb, rn, false, 2 * l + P0, beta, tsw, acc, bad);
+        column_half<T, L, P1, 0>(c, lds, hb, rn, w, 2 * l + P1, beta, tsw, acc, bad);
+    };
+    const auto heat = [&](int i0, int i1) {
+        for (int i = i0; i < i1; ++i) {
+            const int l = ADJ ? n_lat - 1 - i : i;
+            column_half<T, L, P0, 1>(c, lds, true, false, false, 2 * l + P0, beta, tsw, acc, bad);
+            column_half<T, L, P1, 1>(c, lds, true, false, false, 2 * l + P1, beta, tsw, acc, bad);
+        }
+    };
+    const auto over = [&](int i0, int i1) {
+        for (int i = i0; i < i1; ++i) {
+            column_half<T, L, P0, 2>(c, lds, false, false, false, 0, beta, tsw, acc, bad);
+            column_half<T, L, P1, 2>(c, lds, false, false, false, 0, beta, tsw, acc, bad);
+        }
+    };
+    const int end = n_lat - tail;
+    if constexpr (!ADJ) {
+        heat(0, n_hb < end ? n_hb : end);
+        over(n_hb < end ? n_hb : end, end);
+        if (tail && n_or > 0 && !renorm) {
+            column_half<T, L, P0, 2>(c, lds, false, false, false, 0, beta, tsw, acc, bad);
+            column_half<T, L, P1, 3>(c, lds, false, false, true, 0, beta, tsw, acc, bad);
+        } else if (tail) {
+            general(end);
+        }
+    } else {
+        if (head) general(0);
+        over(head, n_or < end ? n_or : end);
+        heat(n_or < end ? n_or : end, end);
+        if (tail) general(end);
+    }
+}
+
+struct ColumnLeg {  // an annealing leg's protocol
+    double a, b;
+    const double* tab;
+    int K;
+    __device__ __forceinline__ double lam(int k) const {  // point k = 0 .. K + 1, ascending for the up-leg
+        if (k <= 0) return a;
+        if (k >= K + 1) return b;
+        return tab ? tab[k - 1] : a + static_cast<double>(k) * (b - a) / static_cast<double>(K + 1);
+    }
+};
+
+// The sweeps of one replica: from `gs`, through n_sweeps sweeps (LEG: the leg's K sweeps at
+// its protocol points, ADJ in adjoint order), to `gd`.  Returns the final energy; W is the
+// leg's work.
+template <typename T, int L, bool LEG, bool ADJ>
+__device__ __forceinline__ double column_run(const hsg_ensemble& e, int slot, const T* __restrict__ gs, T* gd, int n_sweeps,
+                                             int n_hb, int n_or, const ColumnLeg& leg, double H, double& W,
+                                             unsigned char* smem_raw, double* red, double& s_H) {
+    using M = Column<T, L>;
+    constexpr int HL = M::HL, PL = M::PL, NH = M::NH, N = M::N, NT = M::NT, ZP = M::ZP, B = M::B;
+    T* lds = reinterpret_cast<T*>(smem_raw);
+    const int tid = static_cast<int>(threadIdx.x);
+    const int R = e.n_temps;
+    const T* J = static_cast<const T*>(e.couplings) + static_cast<size_t>(slot / (e.n_chains * R)) * 3 * N;
+    const uint32_t t0 = e.sweep_ctr[slot];
+    ColumnState<T, L> c;
+    c.J = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(J), 0, 3 * N * B, 0x00027000);
+    c.g = e.slot_base + static_cast<uint32_t>(slot);
+    c.k0 = static_cast<int>(key_lo(e.seed));
+    c.k1 = static_cast<int>(key_hi(e.seed));
+    c.on = tid < PL * M::ZG;
+    {
+        const int t = c.on ? tid : PL * M::ZG - 1;
+        const int zg = t / PL, q = t - zg * PL;
+        const int j = q / HL, ih = q - j * HL;
+        const int z0 = zg * ZP, base = z0 * PL;
+        const int q_xp = j * HL + (ih + 1 == HL ? 0 : ih + 1), q_xm = j * HL + (ih == 0 ? HL - 1 : ih - 1);
+        const int q_yp = (j + 1 == L ? 0 : j + 1) * HL + ih, q_ym = (j == 0 ? L - 1 : j - 1) * HL + ih;
+        c.own = (base + q) * B;
+        c.o0 = (j + z0) & 1;
+#pragma unroll
+        for (int v = 0; v < 2; ++v) {
+            const int o = v ^ ((j + z0) & 1);
+            c.x[v][0] = (base + (o ? q_xp : q)) * B;
+            c.x[v][1] = (base + (o ? q : q_xm)) * B;
+            c.x[v][2] = (base + (o ? q_xp : q_xm)) * B;
+        }
+        c.yp = (base + q_yp) * B;
+        c.ym = (base + q_ym) * B;
+        c.zm = ((z0 == 0 ? L - 1 : z0 - 1) * PL + q) * B;
+        c.zp = ((z0 + ZP == L ? 0 : z0 + ZP) * PL + q) * B;
+    }
+    const int own = c.own / B;
+    // a sweep that opens with a heat-bath half-sweep of parity 0 reads no parity-0 spin
+    const bool skip0 = n_hb > 0 && !ADJ;
+    const auto load = [&](int p) {
+#pragma unroll
+        for (int m = 0; m < ZP; ++m)
+#pragma unroll
+            for (int mu = 0; mu < 3; ++mu) c.s[p][m][mu] = gs[(mu * 2 + p) * NH + own + m * PL];
+    };
+    load(1);
+    if (!skip0) {
+        load(0);
+    } else {
+#pragma unroll
+        for (int m = 0; m < ZP; ++m) c.s[0][m][0] = c.s[0][m][1] = c.s[0][m][2] = T(0);
+    }
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+        c.jz[p][0] = J[(4 + p) * NH + c.zm / B];
+#pragma unroll
+        for (int m = 0; m < ZP; ++m) c.jz[p][m + 1] = J[(4 + p) * NH + own + m * PL];
+    }
+    constexpr int FIRST = ADJ ? 1 : 0;  // the sublattice updated first
+    column_bonds<T, L, FIRST>(c, c.jb[0], 0, 0);
+    column_bonds<T, L, FIRST>(c, c.jb[1], 1, 0);
+    if (c.on) {
+#pragma unroll
+        for (int m = 0; m < ZP; ++m)
+#pragma unroll
+            for (int mu = 0; mu < 3; ++mu) lds[mu * NH + own + m * PL] = c.s[1 - FIRST][m][mu];
+    }
+    lds_barrier();
+
+    const bool renorm = renorm_on(e) && n_hb == 0;
+    const int n_iter = LEG ? leg.K + 1 : n_sweeps;
+    bool bad = false;
+    for (int k = 0; k < n_iter; ++k) {
+        double beta_d;
+        if (LEG) {
+            const double cur = ADJ ? leg.lam(leg.K + 1 - k) : leg.lam(k);
+            beta_d = ADJ ? leg.lam(leg.K - k) : leg.lam(k + 1);
+            W += (beta_d - cur) * H;
+            if (k == leg.K) break;
+        } else {
+            beta_d = e.betas[label(e.temp_of_slot[slot], R, e.guard)];
+        }
+        const bool need_e = LEG || k == n_sweeps - 1;
+        double acc = 0.0;
+        column_sweep<T, L, ADJ>(c, lds, n_hb, n_or, renorm, need_e, static_cast<T>(beta_d), t0 + static_cast<uint32_t>(k),
+                                acc, bad);
+        if (need_e) {
+            const double tot = block_sum<NT, true>(acc, red);
+            if (tid == 0) s_H = -tot;
+            lds_barrier();
+            H = s_H;
+        }
+    }
+    if (bad || !isfinite(H)) atomicOr(e.guard, 1);
+    if (c.on) {
+#pragma unroll
+        for (int p = 0; p < 2; ++p)
+#pragma unroll
+            for (int m = 0; m < ZP; ++m)
+#pragma unroll
+                for (int mu = 0; mu < 3; ++mu) gd[(mu * 2 + p) * NH + own + m * PL] = c.s[p][m][mu];
+    }
+    if (tid == 0) e.sweep_ctr[slot] = t0 + static_cast<uint32_t>(LEG ? leg.K : n_sweeps);
+    return H;
+}
+
+// Regular sweeps, one workgroup per replica.
+template <typename T, int L>
+__global__ void __launch_bounds__((Column<T, L>::NT), (Column<T, L>::WPE))
+    k_column(hsg_ensemble e, int n_sweeps, int n_hb, int n_or) {
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    __shared__ double red[Column<T, L>::NT / 64];
+    __shared__ double s_H;
+    const int slot = xcd_order(static_cast<int>(blockIdx.x), static_cast<int>(gridDim.x));
+    T* gs = static_cast<T*>(e.spins) + static_cast<size_t>(slot) * 3 * Column<T, L>::N;
+    double W = 0.0;
+    const double H = column_run<T, L, false, false>(e, slot, gs, gs, n_sweeps, n_hb, n_or, ColumnLeg{}, 0.0, W, smem_raw,
+                                                    red, s_H);
+    if (threadIdx.x == 0) e.energy[slot] = H;
+}
+
+// Annealing legs of the pairs i = parity (mod 2), one workgroup per (chain, pair, leg),
+// from the spins into the candidate buffer.
+template <typename T, int L>
+__global__ void __launch_bounds__((Column<T, L>::NT), (Column<T, L>::WPE))
+    k_column_leg(hsg_ensemble e, int n_hb, int n_or, int parity) {
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    __shared__ double red[Column<T, L>::NT / 64];
+    __shared__ double s_H;
+    constexpr int N = Column<T, L>::N;
+    const int R = e.n_temps;
+    const int bid = xcd_order(static_cast<int>(blockIdx.x), static_cast<int>(gridDim.x));
+    const int npp = (R - parity) / 2;
+    const int down = bid & 1, rest = bid >> 1, ch = rest / npp;
+    const int ipair = parity + 2 * (rest % npp);
+    const int slot = ch * R + label(e.slot_of_temp[ch * R + ipair + down], R, e.guard);
+    ColumnLeg leg;
+    leg.K = e.anneal_K[ipair];
+    if (leg.K < 0 || leg.K > e.anneal_K_max) {
+        if (threadIdx.x == 0) atomicOr(e.guard, 2);
+        leg.K = leg.K < 0 ? 0 : e.anneal_K_max;
+    }
+    leg.a = e.betas[ipair];
+    leg.b = e.betas[ipair + 1];
+    leg.tab = e.anneal_lambda ? e.anneal_lambda + static_cast<size_t>(ipair) * e.anneal_K_max : nullptr;
+    const ScratchLayout sl = scratch_layout(e);
+    unsigned char* scr = static_cast<unsigned char*>(e.scratch);
+    double H = e.energy[slot], W = 0.0;
+    const T* gs = static_cast<const T*>(e.spins) + static_cast<size_t>(slot) * 3 * N;
+    T* gd = reinterpret_cast<T*>(scr + sl.cand) + static_cast<size_t>(slot) * 3 * N;
+    if (leg.K == 0)
+        W = down ? (leg.a - leg.b) * H : (leg.b - leg.a) * H;
+    else if (down)
+        H = column_run<T, L, true, true>(e, slot, gs, gd, 0, n_hb, n_or, leg, H, W, smem_raw, red, s_H);
+    else
+        H = column_run<T, L, true, false>(e, slot, gs, gd, 0, n_hb, n_or, leg, H, W, smem_raw, red, s_H);
+    if (threadIdx.x == 0) {
+        e.work[(static_cast<size_t>(ch) * (R - 1) + ipair) * 2 + down] = W;
+        reinterpret_cast<double*>(scr + sl.cand_energy)[slot] = H;
+    }
+}
+
+template <typename T, int L>
+static hipError_t go_column(const hsg_ensemble& e, int n_sweeps, int n_hb, int n_or, hipStream_t st) {
+    using M = Column<T, L>;
+    auto kern = k_column<T, L>;
+    const hipError_t err = allow_dynamic_lds(reinterpret_cast<const void*>(kern), M::LDS);
+    if (err != hipSuccess) return err;
+    hipLaunchKernelGGL(kern, dim3(e.n_samples * e.n_chains * e.n_temps), dim3(M::NT), M::LDS, st, e, n_sweeps, n_hb, n_or);
+    return hipGetLastError();
+}
+
+template <typename T, int L>
+static hipError_t go_column_legs(const hsg_ensemble& e, int parity, int n_hb, int n_or, hipStream_t st) {
+    using M = Column<T, L>;
+    const int blocks = e.n_samples * e.n_chains * ((e.n_temps - parity) / 2) * 2;
+    if (blocks <= 0) return hipSuccess;
+    auto kern = k_column_leg<T, L>;
+    const hipError_t err = allow_dynamic_lds(reinterpret_cast<const void*>(kern), M::LDS);
+    if (err != hipSuccess) return err;
+    hipLaunchKernelGGL(kern, dim3(blocks), dim3(M::NT), M::LDS, st, e, n_hb, n_or, parity);
+    return hipGetLastError();
+}
+
+// Binary32 L = 18 .. 26 and binary64 L = 16, 18: where the registers and LDS of a CU hold
+// the replica (beyond, a thread's spins alone exceed its registers).
+bool column_supported(const hsg_ensemble& e) {
+    if (max_block_lds() < 160 * 1024) return false;
+    if (e.precision == HSG_FP64) return e.L == 16 || e.L == 18;
+    return e.L >= 18 && e.L <= 26 && (e.L & 1) == 0;
+}
+
+// ... and where it was measured faster than the streaming kernels, which pay per
+// half-sweep where this one pays once for bringing a replica in and out: everywhere but
+// at the largest lattices (whose registers spill) for calls of a few lattice sweeps.
+// Column / streaming in us, 10, 54 and 432 replicas: binary32 L = 24, 1 + 1 lattice sweeps
+// 38 / 27, 39 / 43, 100 / 97; 1 + 3: 49 / 43, 51 / 78, 127 / 184; 1 + 30: 212 / 291,
+// 211 / 549, 448 / 1357.  L = 26, 1 + 3: 71 / 47, 79 / 89, 193 / 255; binary64 L = 18,
+// 1 + 1: 44 / 36, 46 / 52, 98 / 117.
+bool column_faster(const hsg_ensemble& e, int n_sweeps, int n_hb, int n_or) {
+    if (!column_supported(e)) return false;
+    const bool spills = e.precision == HSG_FP64 ? e.L == 18 : e.L >= 24;
+    if (!spills) return true;
+    const long long lattice_sweeps = static_cast<long long>(n_sweeps) * (n_hb + n_or);
+    const long long slots = static_cast<long long>(e.n_samples) * e.n_chains * e.n_temps;
+    return lattice_sweeps >= (slots < 32 ? 8 : 4);
+}
+
+hipError_t launch_column_sweeps(const hsg_ensemble& e, int n_sweeps, int n_hb, int n_or, hipStream_t st) {
+    if (e.precision == HSG_FP64)
+        return e.L == 16 ? go_column<double, 16>(e, n_sweeps, n_hb, n_or, st)
+                         : go_column<double, 18>(e, n_sweeps, n_hb, n_or, st);
+    switch (e.L) {
+        case 18: return go_column<float, 18>(e, n_sweeps, n_hb, n_or, st);
+        case 20: return go_column<float, 20>(e, n_sweeps, n_hb, n_or, st);
+        case 22: return go_column<float, 22>(e, n_sweeps, n_hb, n_or, st);
+        case 24: return go_column<float, 24>(e, n_sweeps, n_hb, n_or, st);
+        default: return go_column<float, 26>(e, n_sweeps, n_hb, n_or, st);
+    }
+}
+
+// (binary64 L = 16 legs run in k_resident_leg)
+hipError_t launch_column_legs(const hsg_ensemble& e, int parity, int n_hb, int n_or, hipStream_t st) {
+    if (e.precision == HSG_FP64)
+        return e.L == 18 ? go_column_legs<double, 18>(e, parity, n_hb, n_or, st) : hipErrorInvalidValue;
+    switch (e.L) {
+        case 18: return go_column_legs<float, 18>(e, parity, n_hb, n_or, st);
+        case 20: return go_column_legs<float, 20>(e, parity, n_hb, n_or, st);
+        case 22: return go_column_legs<float, 22>(e, parity, n_hb, n_or, st);
+        case 24: return go_column_legs<float, 24>(e, parity, n_hb, n_or, st);
+        default: return go_column_legs<float, 26>(e, parity, n_hb, n_or, st);
+    }
+}
+
+}  // namespace hsg
