@@ -80,35 +80,90 @@ __global__ void k_mlp_errors(const float* __restrict__ p, int I, int H, int O, f
     }
 }
 
-// One thread per parameter; sums over the batch in sample order.
-__global__ void k_mlp_param_grad(int I, int H, int O, const float* __restrict__ x, int B,
-                                 const float* __restrict__ acts, const float* __restrict__ dy,
-                                 float* __restrict__ dp) {
+// Gradients, summed over the batch in sample order: every parameter's gradient is a chain
+// sum_b u_b v_b, with u one unit's (or output's) error and v a row of activations or inputs
+// (a bias: u = 1, v the errors).  A wave owns 64 columns of one such row and a workgroup
+// four rows with the same v, so that 64 samples of v and u at a time are fetched by the
+// whole workgroup, the next 64 in flight while the chains run over these from LDS.  The
+// chain itself (a multiply-add and its LDS reads per sample) is then what bounds it; a
+// thread per parameter fetching its own operands waited for memory at every few samples:
+// 127 us at B = 560, H = 64 against 8 us.
+constexpr int kGradSamples = 64;
+
+struct GradTask {
+    const float *u, *v;  // u: nullptr for 1
+    size_t us, vs;       // strides per sample
+    float* out;
+    int row0, n_rows, out_stride, n_cols;
+};
+
+__device__ __forceinline__ GradTask grad_task(int id, int I, int H, int O, const float* x, const float* acts,
+                                              const float* dy, float* dp) {
     const MlpOffsets o = mlp_offsets(I, H, O);
-    const int id = blockIdx.x * blockDim.x + threadIdx.x;
-    if (id >= o.total) return;
-    float s = 0.0f;
     const size_t A = static_cast<size_t>(4) * H;
-    if (id < o.b1) {  // W1[j][i]
-        const int j = (id - o.W1) / I, i = (id - o.W1) % I;
-        for (int b = 0; b < B; ++b) s = fmaf(acts[b * A + 2 * H + j], x[static_cast<size_t>(b) * I + i], s);
-    } else if (id < o.W2) {  // b1[j]
-        const int j = id - o.b1;
-        for (int b = 0; b < B; ++b) s += acts[b * A + 2 * H + j];
-    } else if (id < o.b2) {  // W2[j][k]
-        const int j = (id - o.W2) / H, k = (id - o.W2) % H;
-        for (int b = 0; b < B; ++b) s = fmaf(acts[b * A + 3 * H + j], acts[b * A + k], s);
-    } else if (id < o.W3) {  // b2[j]
-        const int j = id - o.b2;
-        for (int b = 0; b < B; ++b) s += acts[b * A + 3 * H + j];
-    } else if (id < o.b3) {  // W3[k][j]
-        const int k = (id - o.W3) / H, j = (id - o.W3) % H;
-        for (int b = 0; b < B; ++b) s = fmaf(dy[static_cast<size_t>(b) * O + k], acts[b * A + H + j], s);
-    } else {  // b3[k]
-        const int k = id - o.b3;
-        for (int b = 0; b < B; ++b) s += dy[static_cast<size_t>(b) * O + k];
+    const int C = (H + 63) / 64, HG = (H + 3) / 4, OG = (O + 3) / 4;
+    const auto rows = [](int g, int n) { return n - 4 * g < 4 ? n - 4 * g : 4; };
+    const auto cols = [&](int c) { return H - 64 * c < 64 ? H - 64 * c : 64; };
+    if (id < HG * C) {  // W2
+        const int g = id / C, c = id - g * C;
+        return {acts + 3 * H, acts + 64 * c, A, A, dp + o.W2 + 64 * c, 4 * g, rows(g, H), H, cols(c)};
     }
-    dp[id] = s;
+    id -= HG * C;
+    if (id < HG) return {acts + 2 * H, x, A, static_cast<size_t>(I), dp + o.W1, 4 * id, rows(id, H), I, I};
+    id -= HG;
+    if (id < OG * C) {  // W3
+        const int g = id / C, c = id - g * C;
+        return {dy, acts + H + 64 * c, static_cast<size_t>(O), A, dp + o.W3 + 64 * c, 4 * g, rows(g, O), H, cols(c)};
+    }
+    id -= OG * C;
+    if (id < C) return {nullptr, acts + 2 * H + 64 * id, 0, A, dp + o.b1 + 64 * id, 0, 1, 0, cols(id)};
+    id -= C;
+    if (id < C) return {nullptr, acts + 3 * H + 64 * id, 0, A, dp + o.b2 + 64 * id, 0, 1, 0, cols(id)};
+    return {nullptr, dy, 0, static_cast<size_t>(O), dp + o.b3, 0, 1, 0, O};
+}
+
+static unsigned grad_tasks(int H, int O) {
+    const int C = (H + 63) / 64, HG = (H + 3) / 4, OG = (O + 3) / 4;
+    return static_cast<unsigned>(HG * C + HG + OG * C + 2 * C + 1);
+}
+
+__global__ void __launch_bounds__(256)
+    k_mlp_param_grad(int I, int H, int O, const float* __restrict__ x, int B, const float* __restrict__ acts,
+                     const float* __restrict__ dy, float* __restrict__ dp) {
+    constexpr int NS = kGradSamples, PV = NS / 4;
+    __shared__ float sv[NS][64];
+    __shared__ __align__(16) float su[4][NS];
+    const GradTask t = grad_task(blockIdx.x, I, H, O, x, acts, dy, dp);
+    const int lane = threadIdx.x & 63, row = threadIdx.x >> 6;
+    const int col = lane < t.n_cols ? lane : t.n_cols - 1;
+    const int urow = t.row0 + (row < t.n_rows ? row : t.n_rows - 1);
+    float rv[PV], ru;
+    const auto fetch = [&](int b0) {
+#pragma unroll
+        for (int k = 0; k < PV; ++k) {
+            const int b = b0 + 4 * k + row;
+            rv[k] = t.v[(b < B ? b : B - 1) * t.vs + col];
+        }
+        const int b = b0 + lane;
+        ru = t.u ? t.u[(b < B ? b : B - 1) * t.us + urow] : 1.0f;
+    };
+    float s = 0.0f;
+    if (B > 0) fetch(0);
+    for (int b0 = 0; b0 < B; b0 += NS) {
+#pragma unroll
+        for (int k = 0; k < PV; ++k) sv[4 * k + row][lane] = rv[k];
+        su[row][lane] = ru;
+        __syncthreads();
+        if (b0 + NS < B) fetch(b0 + NS);
+        if (b0 + NS <= B) {
+#pragma unroll
+            for (int k = 0; k < NS; ++k) s = fmaf(su[row][k], sv[k][lane], s);
+        } else {
+            for (int k = 0; k < B - b0; ++k) s = fmaf(su[row][k], sv[k][lane], s);
+        }
+        __syncthreads();
+    }
+    if (row < t.n_rows && lane < t.n_cols) t.out[static_cast<size_t>(t.row0 + row) * t.out_stride + lane] = s;
 }
 
 __global__ void k_mlp_adam(float* p, const float* g, float* m, float* v, int n, float lr,
@@ -164,11 +219,9 @@ hipError_t launch_mlp_forward(const float* p, int I, int H, int O, const float* 
 
 hipError_t launch_mlp_backward(const float* p, int I, int H, int O, const float* x, int B,
                                float* acts, const float* dy, float* dp, hipStream_t st) {
-    const MlpOffsets o = mlp_offsets(I, H, O);
     if (B > 0)
         hipLaunchKernelGGL(k_mlp_errors, dim3(B), dim3(mlp_threads(H, O, I)), 0, st, p, I, H, O, acts, dy);
-    hipLaunchKernelGGL(k_mlp_param_grad, dim3((o.total + 255) / 256), dim3(256), 0, st, I, H, O, x, B,
-                       acts, dy, dp);
+    hipLaunchKernelGGL(k_mlp_param_grad, dim3(grad_tasks(H, O)), dim3(256), 0, st, I, H, O, x, B, acts, dy, dp);
     return hipGetLastError();
 }
 
