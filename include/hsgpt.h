@@ -114,7 +114,7 @@ typedef struct hsg_ensemble {
 /* Tuning knobs of the sweep kernels (0 = library default). */
 typedef struct hsg_tuning {
     int32_t path;           /* 0 auto: the register-resident kernel where it is the faster
-                               one (binary32 L = 18 .. 26, binary64 L = 16 and 18; not with
+                               one (binary32 L = 18 .. 32, binary64 L = 16 and 18; not with
                                block_threads or replicas_per_block set), else 3 if a replica
                                fits in one workgroup's LDS, else 2;
                                1 LDS-resident lattice on persistent double-buffered

@@ -1,24 +1,32 @@
 // Register-resident sweeps for lattices around and beyond one workgroup's LDS: binary32
-// L = 18 .. 26, binary64 L = 16 and 18.
+// L = 18 .. 32, binary64 L = 16 and 18.
 //
 // One workgroup owns one replica for the whole call.  Thread (g, q) owns the sites of both
 // sublattices at place q = ih + (L/2) j of the planes z = g ZP .. g ZP + ZP - 1: their spins
 // stay in its registers, so two of a site's neighbours along z are its own (other
 // sublattice, same place, planes z - 1 and z + 1) and only those in the plane, and the
-// ones beyond its run of planes, come from LDS.  LDS holds one sublattice at a time, the
-// one the current half-sweep reads: a half-sweep reads it, waits, and writes the updated
-// sublattice over it.  HBM sees one read and one write of the replica per call, however
-// many sweeps it makes, where the streaming kernels move three half-replicas per
-// half-sweep.  The couplings along z stay in registers too; the other four of a site come
-// from the L2 in every half-sweep, asked for two sites ahead.  Binary32 heat-bath
-// half-sweeps draw the uniforms first, one Philox block per site pair, into LDS (where it
-// has room for them).
+// ones beyond its run of planes, come from LDS.  HBM sees one read and one write of the
+// replica per call, however many sweeps it makes, where the streaming kernels move three
+// half-replicas per half-sweep.
+//
+// To L = 26, LDS holds one sublattice at a time, the one the current half-sweep reads: a
+// half-sweep reads it, waits, and writes the updated sublattice over it.  The couplings
+// along z stay in registers too; the other four of a site come from the L2 in every
+// half-sweep, asked for two sites ahead.  Binary32 heat-bath half-sweeps draw the uniforms
+// first, one Philox block per site pair, into LDS (where it has room for them).
+//
+// From L = 28, a sublattice is more than an LDS and the spins leave no registers for
+// couplings (L = 32: 192 of a thread's 256).  A thread owns whole columns there (no plane
+// is beyond its run), LDS holds BZ planes of a sublattice at a time in two buffers in
+// turn, and all six couplings come from the L2.
 //
 // What bounds it (L = 24, 8 x 2 x 16 replicas, one per CU): an overrelaxation half-sweep
 // takes 2.9 us, in which the VALU is 51 % and the LDS 47 % busy, the two only partly
-// overlapping between the barriers of the one workgroup a CU holds.  1 heat-bath + 30
-// overrelaxation lattice sweeps of 8 x 2 x 27 replicas: 0.46 ms, against 1.42 ms in 62
-// streaming launches at the rate of HBM.
+// overlapping between the barriers of the one workgroup a CU holds (L = 28: 6.5 us, 41 and
+// 39 %, two waves per SIMD).  1 heat-bath + 30 overrelaxation lattice sweeps of 8 x 2 x 27
+// replicas: L = 24 0.42 ms, against 1.36 ms in 62 streaming launches at the rate of HBM;
+// L = 28 0.89 against 2.16 ms; L = 32 1.04 against 2.71 ms.  A CU holds one replica, so
+// that replicas beyond a multiple of 256 wait for a round of their own.
 //
 // Spins are those of the other sweep kernels bit for bit (same site arithmetic, order of
 // the field's terms and random numbers).
@@ -26,25 +34,32 @@
 #include "hsg_launch.h"
 
 #include <type_traits>
+#include <utility>
 
 namespace hsg {
 
 // ZP planes per run; WPE waves per SIMD the registers are budgeted for; SEL: the neighbour
 // along x that is the thread's own is taken from its registers (two selects per component)
 // instead of LDS; FENCE: bits 1, 2, 4 keep the compiler from mixing a site's loads with its
-// arithmetic, a site with the next, two sites with the next two (measured per size).
+// arithmetic, a site with the next, two sites with the next two; bit 8 has threads without
+// sites skip the writes to LDS that they otherwise repeat (the compiler spills less without
+// the branch but at L = 26; all measured per size).  BZ, HZ: planes per buffer of an
+// overrelaxation and of each half of a heat-bath half-sweep of whole columns.
 template <typename T, int L>
 struct ColumnShape;
-template <int ZP_, int WPE_, bool SEL_, int FENCE_>
+template <int ZP_, int WPE_, bool SEL_, int FENCE_, int BZ_ = 0, int HZ_ = 0>
 struct ColumnTuning {
-    static constexpr int ZP = ZP_, WPE = WPE_, FENCE = FENCE_;
+    static constexpr int ZP = ZP_, WPE = WPE_, FENCE = FENCE_, BZ = BZ_, HZ = HZ_;
     static constexpr bool SEL = SEL_;
 };
 template <> struct ColumnShape<float, 18> : ColumnTuning<6, 4, true, 4> {};   // two workgroups per CU
 template <> struct ColumnShape<float, 20> : ColumnTuning<4, 4, true, 4> {};
 template <> struct ColumnShape<float, 22> : ColumnTuning<11, 2, false, 3> {};
 template <> struct ColumnShape<float, 24> : ColumnTuning<8, 4, false, 3> {};
-template <> struct ColumnShape<float, 26> : ColumnTuning<13, 3, false, 3> {};
+template <> struct ColumnShape<float, 26> : ColumnTuning<13, 3, false, 11> {};
+template <> struct ColumnShape<float, 28> : ColumnTuning<28, 2, false, 3, 7, 7> {};
+template <> struct ColumnShape<float, 30> : ColumnTuning<30, 2, false, 3, 5, 5> {};
+template <> struct ColumnShape<float, 32> : ColumnTuning<32, 2, false, 3, 4, 4> {};
 template <> struct ColumnShape<double, 16> : ColumnTuning<4, 2, false, 2> {};
 template <> struct ColumnShape<double, 18> : ColumnTuning<6, 2, false, 3> {};
 
@@ -55,10 +70,19 @@ struct Column : ColumnShape<T, L> {
     static constexpr int ZG = L / ZP;                      // runs of planes
     static constexpr int NT = ((PL * ZG + 63) / 64) * 64;  // threads
     static constexpr int B = static_cast<int>(sizeof(T));
-    // LDS: one sublattice [3][NH], and the heat-bath uniforms [2][NH] of a half-sweep
-    static constexpr bool DRAWN = sizeof(T) == 4 && 5 * NH * 4 <= 150 * 1024;
-    static constexpr size_t LDS = static_cast<size_t>(DRAWN ? 5 : 3) * NH * sizeof(T);
+    // LDS: one sublattice [3][NH], and the heat-bath uniforms [2][NH] of a half-sweep; or
+    // (BZ > 0) two batches of BZ planes of a sublattice, [2][3][BZ PL]
+    static constexpr int BZ = ColumnShape<T, L>::BZ, NB = BZ ? L / BZ : 1;
+    static constexpr int CS = BZ ? BZ * PL : NH;  // from one component to the next
+    static constexpr bool DRAWN = sizeof(T) == 4 && BZ == 0 && 5 * NH * 4 <= 150 * 1024;
+    static constexpr bool JZ = BZ == 0;  // bonds along z in registers
+    static constexpr int JN = JZ ? 4 : 6;
+    static constexpr int HZ = ColumnShape<T, L>::HZ;  // planes of each half of the lattice per heat-bath step (BZ > 0)
+    static constexpr size_t LDS = (BZ ? (12 * HZ + 12 > 6 * BZ ? 12 * HZ + 12 : 6 * BZ) * static_cast<size_t>(PL)
+                                      : (DRAWN ? 5 : 3) * static_cast<size_t>(NH)) *
+                                  sizeof(T);
     static_assert(L % ZP == 0 && ZP >= 2 && NT <= 1024, "one workgroup");
+    static_assert(BZ == 0 || (ZG == 1 && L % BZ == 0 && NB % 2 == 0), "whole columns, batches in turn in two buffers");
 };
 
 __device__ __forceinline__ float buffer_get(__amdgpu_buffer_rsrc_t r, int voff, int soff, float) {
@@ -70,32 +94,60 @@ __device__ __forceinline__ double buffer_get(__amdgpu_buffer_rsrc_t r, int voff,
     return __hiloint2double(static_cast<int>(v.y), static_cast<int>(v.x));
 }
 
+// f(integral_constant m) for m = 0 .. N - 1, unrolled whatever the size of f.
+template <class F, int... Ms>
+__device__ __forceinline__ void each_plane_of(std::integer_sequence<int, Ms...>, F&& f) {
+    (f(std::integral_constant<int, Ms>{}), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void each_plane(F&& f) {
+    each_plane_of(std::make_integer_sequence<int, N>{}, f);
+}
+
 // What a thread keeps for the whole call.
 template <typename T, int L>
 struct ColumnState {
     static constexpr int ZP = Column<T, L>::ZP;
     T s[2][ZP][3];    // spins [sublattice][plane of the run][component]
-    T jb[2][4];       // couplings in the plane of the next two sites to update
-    T jz[2][ZP + 1];  // bonds along z: [sublattice of the lower end][plane - first plane + 1]
+    T jb[2][Column<T, L>::JN];                 // couplings of the next two sites to update
+    T jz[2][Column<T, L>::JZ ? ZP + 1 : 1];  // bonds along z: [sublattice of the lower end][plane - first plane + 1]
     // byte offsets of sites in a sublattice's array, in LDS and of the couplings alike: own
     // site of the run's first plane; [(P + m) & 1][+x, -x] (SEL: [..][2] is the one that is
     // not the thread's own); y neighbours; the planes below and above the run
     int own, x[2][3], yp, ym, zm, zp;
-    bool on, o0;  // a thread with sites; x = 2 ih + o with o = o0 where (P + m) is even
+    // a thread without sites of its own (!on) repeats the last one's: it writes the same
+    // values to the same places, and only its energies are left out
+    bool on;
+    bool o0;  // x = 2 ih + o with o = o0 where (P + m) is even
     __amdgpu_buffer_rsrc_t J;
     uint32_t g;
     int k0, k1;
 };
 
-// The couplings in the plane of the site of sublattice P in plane m of the run.
+// The couplings of the site of sublattice P in plane m of the run that registers do not hold.
 template <typename T, int L, int P>
-__device__ __forceinline__ void column_bonds(const ColumnState<T, L>& c, T (&j)[4], int m, int so) {
+__device__ __forceinline__ void column_bonds(const ColumnState<T, L>& c, T (&j)[Column<T, L>::JN], int m, int so) {
     using M = Column<T, L>;
     constexpr int PL = M::PL, NH = M::NH, Q = 1 - P, B = M::B;
     j[0] = buffer_get(c.J, c.own, so + (P * NH + m * PL) * B, T());
     j[1] = buffer_get(c.J, c.x[(P + m) & 1][1], so + (Q * NH + m * PL) * B, T());
     j[2] = buffer_get(c.J, c.own, so + ((2 + P) * NH + m * PL) * B, T());
     j[3] = buffer_get(c.J, c.ym, so + ((2 + Q) * NH + m * PL) * B, T());
+    if constexpr (!M::JZ) {
+        j[4] = buffer_get(c.J, c.own, so + ((4 + P) * NH + m * PL) * B, T());
+        j[5] = buffer_get(c.J, c.own, so + ((4 + Q) * NH + (m > 0 ? m - 1 : L - 1) * PL) * B, T());
+    }
+}
+// Batch b (mod NB) of sublattice P into its buffer.
+template <typename T, int L, int P>
+__device__ __forceinline__ void column_publish(const ColumnState<T, L>& c, T* __restrict__ lds, int b) {
+    using M = Column<T, L>;
+#pragma unroll
+    for (int k = 0; k < M::BZ; ++k)
+#pragma unroll
+        for (int mu = 0; mu < 3; ++mu)
+            *reinterpret_cast<T*>(reinterpret_cast<unsigned char*>(lds) + c.own +
+                                  (((b & 1) * 3 + mu) * M::CS + k * M::PL) * M::B) = c.s[P][b * M::BZ + k][mu];
 }
 
 // One half-sweep of sublattice P: KIND 1 heat-bath, 2 overrelaxation, 3 overrelaxation
@@ -104,7 +156,7 @@ template <typename T, int L, int P, int KIND>
 __device__ __forceinline__ void column_half(ColumnState<T, L>& c, T* __restrict__ lds, bool hb_arg, bool rn_arg,
                                             bool want_arg, int hs, T beta, uint32_t tsw, double& acc, bool& bad) {
     using M = Column<T, L>;
-    constexpr int PL = M::PL, NH = M::NH, NQ = M::NQ, ZP = M::ZP, NT = M::NT, Q = 1 - P;
+    constexpr int PL = M::PL, NH = M::NH, NQ = M::NQ, ZP = M::ZP, NT = M::NT, Q = 1 - P, BZ = M::BZ;
     const bool hb = KIND == 0 ? hb_arg : KIND == 1;
     const bool rn = KIND == 0 && rn_arg;
     const bool want = KIND == 3 || (KIND == 0 && want_arg);
@@ -128,16 +180,24 @@ __device__ __forceinline__ void column_half(ColumnState<T, L>& c, T* __restrict_
         }
         lds_barrier();
     }
+    each_plane<ZP>([&](auto mc) __attribute__((always_inline)) {
+        constexpr int m = decltype(mc)::value;
+        constexpr int e = (P + m) & 1;
+        if constexpr (BZ > 0 && m % (BZ > 0 ? BZ : 1) == 0) {  // the next batch, which the barrier below completes
+            if constexpr (m + BZ < ZP)
+                column_publish<T, L, Q>(c, lds, m / (BZ > 0 ? BZ : 1) + 1);
+            else
+                column_publish<T, L, P>(c, lds, 0);  // (of the sublattice the next half-sweep reads)
+        }
+        T j[M::JN];
 #pragma unroll
-    for (int m = 0; m < ZP; ++m) {
-        const int e = (P + m) & 1;
-        T j[4];
-#pragma unroll
-        for (int d = 0; d < 4; ++d) j[d] = c.jb[m & 1][d];
+        for (int d = 0; d < M::JN; ++d) j[d] = c.jb[m & 1][d];
         T n[4][3], zlo[3], zhi[3];
 #pragma unroll
         for (int mu = 0; mu < 3; ++mu) {
-            const int pl = mu * NH + m * PL;
+            // the plane's place in LDS
+            const int pl = BZ > 0 ? ((m / (BZ > 0 ? BZ : 1) & 1) * 3 + mu) * M::CS + m % (BZ > 0 ? BZ : 1) * PL
+                                  : mu * NH + m * PL;
             if constexpr (M::SEL) {
                 const T far = at(c.x[e][2], pl), near = c.s[Q][m][mu];
                 const bool o = e ? !c.o0 : c.o0;
@@ -149,11 +209,16 @@ __device__ __forceinline__ void column_half(ColumnState<T, L>& c, T* __restrict_
             }
             n[2][mu] = at(c.yp, pl);
             n[3][mu] = at(c.ym, pl);
-            zlo[mu] = m > 0 ? c.s[Q][m > 0 ? m - 1 : 0][mu] : at(c.zm, mu * NH);
-            zhi[mu] = m + 1 < ZP ? c.s[Q][m + 1 < ZP ? m + 1 : 0][mu] : at(c.zp, mu * NH);
+            if constexpr (M::ZG == 1) {
+                zlo[mu] = c.s[Q][m > 0 ? m - 1 : ZP - 1][mu];
+                zhi[mu] = c.s[Q][m + 1 < ZP ? m + 1 : 0][mu];
+            } else {
+                zlo[mu] = m > 0 ? c.s[Q][m > 0 ? m - 1 : 0][mu] : at(c.zm, mu * NH);
+                zhi[mu] = m + 1 < ZP ? c.s[Q][m + 1 < ZP ? m + 1 : 0][mu] : at(c.zp, mu * NH);
+            }
         }
         // the couplings of the site after next
-        if (m + 2 < ZP) column_bonds<T, L, P>(c, c.jb[m & 1], m + 2, so);
+        if constexpr (m + 2 < ZP) column_bonds<T, L, P>(c, c.jb[m & 1], m + 2, so);
         if (M::FENCE & 1) __builtin_amdgcn_sched_barrier(0);
         T S[3];
 #pragma unroll
@@ -161,8 +226,8 @@ __device__ __forceinline__ void column_half(ColumnState<T, L>& c, T* __restrict_
             T v = T(0);
 #pragma unroll
             for (int d = 0; d < 4; ++d) v = fma(j[d], n[d][mu], v);
-            v = fma(c.jz[P][m + 1], zhi[mu], v);
-            v = fma(c.jz[Q][m], zlo[mu], v);
+            v = fma(M::JZ ? c.jz[P][M::JZ ? m + 1 : 0] : j[M::JN - 2], zhi[mu], v);
+            v = fma(M::JZ ? c.jz[Q][M::JZ ? m : 0] : j[M::JN - 1], zlo[mu], v);
             S[mu] = v;
         }
         T ox, oy, oz;
@@ -193,24 +258,114 @@ __device__ __forceinline__ void column_half(ColumnState<T, L>& c, T* __restrict_
         c.s[P][m][0] = ox;
         c.s[P][m][1] = oy;
         c.s[P][m][2] = oz;
-        if (want && c.on) {
+        if (want) {
             const double dx = ox, dy = oy, dz = oz;
             acc += fma(dz, static_cast<double>(S[2]), fma(dy, static_cast<double>(S[1]), dx * static_cast<double>(S[0])));
             const double n2 = fma(dz, dz, fma(dy, dy, dx * dx));
             if (!(fabs(n2 - 1.0) <= NormTol<T>::value)) bad = true;
+            asm volatile("" : "+v"(acc));  // or the sums are put off and every spin and field held for them
         }
         if ((M::FENCE & 2) || ((M::FENCE & 4) && (m & 1))) __builtin_amdgcn_sched_barrier(0);
-    }
+        if (BZ > 0 && m % (BZ > 0 ? BZ : 1) == BZ - 1 && m + 1 < ZP) lds_barrier();
+    });
     // the couplings of the next half-sweep's first two sites
     column_bonds<T, L, Q>(c, c.jb[0], 0, so);
     column_bonds<T, L, Q>(c, c.jb[1], 1, so);
     lds_barrier();  // every thread has read the other sublattice
-    if (c.on) {
+    if constexpr (BZ == 0) {
+        if ((M::FENCE & 8) == 0 || c.on) {
 #pragma unroll
-        for (int m = 0; m < ZP; ++m)
+            for (int m = 0; m < ZP; ++m)
 #pragma unroll
-            for (int mu = 0; mu < 3; ++mu) at(c.own, mu * NH + m * PL) = c.s[P][m][mu];
+                for (int mu = 0; mu < 3; ++mu) at(c.own, mu * NH + m * PL) = c.s[P][m][mu];
+        }
+        lds_barrier();
     }
+}
+
+// A heat-bath half-sweep of sublattice P where a thread owns whole columns (BZ > 0).  Site
+// pairs (h, h + N/4), L/2 planes apart, share a Philox block, so planes z and z + L/2 go
+// together, HZ of each at a time: these planes of the other sublattice and the ones next
+// to them go into LDS, the sites are then updated in a loop (one body instead of one per
+// plane: unrolled like the overrelaxation it would not stay in the instruction cache), and
+// their new spins return to the registers through LDS.
+template <typename T, int L, int P>
+__device__ __forceinline__ void column_heat(ColumnState<T, L>& c, T* __restrict__ lds, int hs, T beta, uint32_t tsw) {
+    using M = Column<T, L>;
+    constexpr int PL = M::PL, NH = M::NH, ZP = M::ZP, B = M::B, HZ = M::HZ, Q = 1 - P, HP = ZP / 2;
+    static_assert(sizeof(T) == 4 && M::ZG == 1, "binary32 columns");
+    int so = 0, k0 = __builtin_amdgcn_readfirstlane(c.k0), k1 = __builtin_amdgcn_readfirstlane(c.k1);
+    asm volatile("" : "+s"(so), "+s"(k0), "+s"(k1));
+    unsigned char* const raw = reinterpret_cast<unsigned char*>(lds);
+    // [half][3][HZ + 2][PL] of sublattice Q, then [half][3][HZ][PL] new spins
+    constexpr int CA = (HZ + 2) * PL * B, CN = HZ * PL * B, NEW = 6 * CA;
+    const auto at = [&](int off) -> T& { return *reinterpret_cast<T*>(raw + off); };
+    const auto bonds = [&](T (&j)[6], int m) {  // of plane m
+        const int x1 = ((P + m) & 1) ? c.x[1][1] : c.x[0][1];
+        const int z = m * PL * B, zd = (m > 0 ? m - 1 : L - 1) * PL * B;
+        j[0] = buffer_get(c.J, c.own, so + P * NH * B + z, T());
+        j[1] = buffer_get(c.J, x1, so + Q * NH * B + z, T());
+        j[2] = buffer_get(c.J, c.own, so + (2 + P) * NH * B + z, T());
+        j[3] = buffer_get(c.J, c.ym, so + (2 + Q) * NH * B + z, T());
+        j[4] = buffer_get(c.J, c.own, so + (4 + P) * NH * B + z, T());
+        j[5] = buffer_get(c.J, c.own, so + (4 + Q) * NH * B + zd, T());
+    };
+    each_plane<HP / HZ>([&](auto bc) __attribute__((always_inline)) {
+        constexpr int z0 = decltype(bc)::value * HZ;
+#pragma unroll
+        for (int half = 0; half < 2; ++half)
+#pragma unroll
+            for (int k = 0; k < HZ + 2; ++k)
+#pragma unroll
+                for (int mu = 0; mu < 3; ++mu)
+                    at(c.own + (half * 3 + mu) * CA + k * PL * B) = c.s[Q][(z0 + half * HP + k - 1 + ZP) % ZP][mu];
+        T jn[2][6];
+        bonds(jn[0], z0);
+        bonds(jn[1], z0 + HP);
+        lds_barrier();
+#pragma unroll 1
+        for (int k = 0; k < HZ; ++k) {
+            T j[2][6];
+#pragma unroll
+            for (int half = 0; half < 2; ++half)
+#pragma unroll
+                for (int d = 0; d < 6; ++d) j[half][d] = jn[half][d];
+            if (k + 1 < HZ) {
+                bonds(jn[0], z0 + k + 1);
+                bonds(jn[1], z0 + k + 1 + HP);
+            }
+            const Words w = philox(static_cast<uint32_t>(c.own / B + (z0 + k) * PL), tsw, c.g, heatbath_c3(hs),
+                                   static_cast<uint32_t>(k0), static_cast<uint32_t>(k1));
+#pragma unroll
+            for (int half = 0; half < 2; ++half) {
+                const int odd = (P + z0 + k + half * HP) & 1;
+                const int xp = odd ? c.x[1][0] : c.x[0][0], xm = odd ? c.x[1][1] : c.x[0][1];
+                const int pl = half * 3 * CA + (k + 1) * PL * B;
+                const int nb[6] = {xp + pl, xm + pl, c.yp + pl, c.ym + pl, c.own + pl + PL * B, c.own + pl - PL * B};
+                T S[3] = {T(0), T(0), T(0)}, o[3];
+#pragma unroll
+                for (int d = 0; d < 6; ++d)
+#pragma unroll
+                    for (int mu = 0; mu < 3; ++mu) S[mu] = fma(j[half][d], at(nb[d] + mu * CA), S[mu]);
+                heatbath<T>(S[0], S[1], S[2], beta, static_cast<T>(u01_23(half ? w.w2 : w.w0)),
+                            static_cast<T>(u01_23(half ? w.w3 : w.w1)), o[0], o[1], o[2]);
+#pragma unroll
+                for (int mu = 0; mu < 3; ++mu) at(NEW + c.own + (half * 3 + mu) * CN + k * PL * B) = o[mu];
+            }
+        }
+#pragma unroll
+        for (int half = 0; half < 2; ++half)
+#pragma unroll
+            for (int k = 0; k < HZ; ++k)
+#pragma unroll
+                for (int mu = 0; mu < 3; ++mu)
+                    c.s[P][z0 + half * HP + k][mu] = at(NEW + c.own + (half * 3 + mu) * CN + k * PL * B);
+        lds_barrier();  // the planes have been read
+    });
+    // the couplings and the batch the next half-sweep starts with
+    column_bonds<T, L, Q>(c, c.jb[0], 0, so);
+    column_bonds<T, L, Q>(c, c.jb[1], 1, so);
+    column_publish<T, L, P>(c, lds, 0);
     lds_barrier();
 }
 
@@ -222,6 +377,22 @@ __device__ __forceinline__ void column_sweep(ColumnState<T, L>& c, T* __restrict
                                              bool want, T beta, uint32_t tsw, double& acc, bool& bad) {
     constexpr int P0 = ADJ ? 1 : 0, P1 = 1 - P0;
     const int n_lat = n_hb + n_or;
+    if constexpr (Column<T, L>::BZ > 0) {  // n_hb > 0 and n_or > 0 (column_faster)
+        static_assert(!ADJ, "no legs on whole columns");
+        for (int l = 0; l < n_hb; ++l) {
+            column_heat<T, L, 0>(c, lds, 2 * l, beta, tsw);
+            column_heat<T, L, 1>(c, lds, 2 * l + 1, beta, tsw);
+        }
+        for (int l = want ? 1 : 0; l < n_or; ++l) {
+            column_half<T, L, 0, 2>(c, lds, false, false, false, 0, beta, tsw, acc, bad);
+            column_half<T, L, 1, 2>(c, lds, false, false, false, 0, beta, tsw, acc, bad);
+        }
+        if (want) {
+            column_half<T, L, 0, 2>(c, lds, false, false, false, 0, beta, tsw, acc, bad);
+            column_half<T, L, 1, 3>(c, lds, false, false, true, 0, beta, tsw, acc, bad);
+        }
+        return;
+    }
     // the lattice sweep that renormalises (the last overrelaxation one of the forward order,
     // where there is no heat-bath) or ends with the energy runs in the general form
     const int head = ADJ && renorm ? 1 : 0, tail = (want || (renorm && !ADJ)) && !(head && n_lat == 1) ? 1 : 0;
@@ -330,6 +501,7 @@ __device__ __forceinline__ double column_run(const hsg_ensemble& e, int slot, co
 #pragma unroll
         for (int m = 0; m < ZP; ++m) c.s[0][m][0] = c.s[0][m][1] = c.s[0][m][2] = T(0);
     }
+    if constexpr (M::JZ)
 #pragma unroll
     for (int p = 0; p < 2; ++p) {
         c.jz[p][0] = J[(4 + p) * NH + c.zm / B];
@@ -339,7 +511,9 @@ __device__ __forceinline__ double column_run(const hsg_ensemble& e, int slot, co
     constexpr int FIRST = ADJ ? 1 : 0;  // the sublattice updated first
     column_bonds<T, L, FIRST>(c, c.jb[0], 0, 0);
     column_bonds<T, L, FIRST>(c, c.jb[1], 1, 0);
-    if (c.on) {
+    if constexpr (M::BZ > 0) {
+        column_publish<T, L, 1 - FIRST>(c, lds, 0);
+    } else {
 #pragma unroll
         for (int m = 0; m < ZP; ++m)
 #pragma unroll
@@ -365,7 +539,7 @@ __device__ __forceinline__ double column_run(const hsg_ensemble& e, int slot, co
         column_sweep<T, L, ADJ>(c, lds, n_hb, n_or, renorm, need_e, static_cast<T>(beta_d), t0 + static_cast<uint32_t>(k),
                                 acc, bad);
         if (need_e) {
-            const double tot = block_sum<NT, true>(acc, red);
+            const double tot = block_sum<NT, true>(c.on ? acc : 0.0, red);
             if (tid == 0) s_H = -tot;
             lds_barrier();
             H = s_H;
@@ -462,28 +636,34 @@ static hipError_t go_column_legs(const hsg_ensemble& e, int parity, int n_hb, in
     return hipGetLastError();
 }
 
-// Binary32 L = 18 .. 26 and binary64 L = 16, 18: where the registers and LDS of a CU hold
+// Binary32 L = 18 .. 32 and binary64 L = 16, 18: where the registers and LDS of a CU hold
 // the replica (beyond, a thread's spins alone exceed its registers).
 bool column_supported(const hsg_ensemble& e) {
     if (max_block_lds() < 160 * 1024) return false;
     if (e.precision == HSG_FP64) return e.L == 16 || e.L == 18;
-    return e.L >= 18 && e.L <= 26 && (e.L & 1) == 0;
+    return e.L >= 18 && e.L <= 32 && (e.L & 1) == 0;
 }
 
-// ... and where it was measured faster than the streaming kernels, which pay per
-// half-sweep where this one pays once for bringing a replica in and out: everywhere but
-// at the largest lattices (whose registers spill) for calls of a few lattice sweeps.
-// Column / streaming in us, 10, 54 and 432 replicas: binary32 L = 24, 1 + 1 lattice sweeps
-// 38 / 27, 39 / 43, 100 / 97; 1 + 3: 49 / 43, 51 / 78, 127 / 184; 1 + 30: 212 / 291,
-// 211 / 549, 448 / 1357.  L = 26, 1 + 3: 71 / 47, 79 / 89, 193 / 255; binary64 L = 18,
-// 1 + 1: 44 / 36, 46 / 52, 98 / 117.
+// ... and where it was measured faster than the streaming kernels.  Those pay per
+// half-sweep, with a launch and at the rate of HBM once the replicas fill it; this one pays
+// once for bringing a replica in and out, and its time hardly depends on the replicas up to
+// one per CU.  So at the larger sizes it takes a few lattice sweeps to win, and for whole
+// columns enough replicas too.  Column / streaming in us at 10, 54, 128 and 432 replicas:
+// binary32 L = 24, 1 + 1 lattice sweeps 38 / 27, 39 / 43, - , 100 / 97; 1 + 3: 49 / 43,
+// 48 / 78, 52 / 78, 106 / 183; 1 + 30: 200 / 296, 202 / 547, 207 / 539, 419 / 1354.
+// L = 28, 1 + 3: 52 / 51, 90 / 84, 93 / 122, 194 / 302; 1 + 30: 437 / 339, 438 / 583,
+// 439 / 856, 888 / 2157.  L = 32, 1 + 3: - , 105 / 77, 111 / 137, 237 / 375; 1 + 30:
+// 507 / 299, 505 / 529, 507 / 979, 1035 / 2713.  Binary64 L = 18, 1 + 1: 44 / 36, 46 / 52,
+// - , 98 / 117; 1 + 30: 161 / 456, 165 / 642, 170 / 550, 347 / 1509.
 bool column_faster(const hsg_ensemble& e, int n_sweeps, int n_hb, int n_or) {
     if (!column_supported(e)) return false;
-    const bool spills = e.precision == HSG_FP64 ? e.L == 18 : e.L >= 24;
-    if (!spills) return true;
+    const bool small = e.precision == HSG_FP64 ? e.L == 16 : e.L <= 22;
+    if (small) return true;
     const long long lattice_sweeps = static_cast<long long>(n_sweeps) * (n_hb + n_or);
     const long long slots = static_cast<long long>(e.n_samples) * e.n_chains * e.n_temps;
-    return lattice_sweeps >= (slots < 32 ? 8 : 4);
+    if (e.L <= 26) return lattice_sweeps >= (slots < 32 ? 8 : 4);
+    // (whole columns neither renormalise nor take the energy after a heat-bath)
+    return n_hb > 0 && n_or > 0 && slots >= 48 && lattice_sweeps >= (slots < 96 ? 20 : 4);
 }
 
 hipError_t launch_column_sweeps(const hsg_ensemble& e, int n_sweeps, int n_hb, int n_or, hipStream_t st) {
@@ -495,7 +675,10 @@ hipError_t launch_column_sweeps(const hsg_ensemble& e, int n_sweeps, int n_hb, i
         case 20: return go_column<float, 20>(e, n_sweeps, n_hb, n_or, st);
         case 22: return go_column<float, 22>(e, n_sweeps, n_hb, n_or, st);
         case 24: return go_column<float, 24>(e, n_sweeps, n_hb, n_or, st);
-        default: return go_column<float, 26>(e, n_sweeps, n_hb, n_or, st);
+        case 26: return go_column<float, 26>(e, n_sweeps, n_hb, n_or, st);
+        case 28: return go_column<float, 28>(e, n_sweeps, n_hb, n_or, st);
+        case 30: return go_column<float, 30>(e, n_sweeps, n_hb, n_or, st);
+        default: return go_column<float, 32>(e, n_sweeps, n_hb, n_or, st);
     }
 }
 
@@ -508,7 +691,8 @@ hipError_t launch_column_legs(const hsg_ensemble& e, int parity, int n_hb, int n
         case 20: return go_column_legs<float, 20>(e, parity, n_hb, n_or, st);
         case 22: return go_column_legs<float, 22>(e, parity, n_hb, n_or, st);
         case 24: return go_column_legs<float, 24>(e, parity, n_hb, n_or, st);
-        default: return go_column_legs<float, 26>(e, parity, n_hb, n_or, st);
+        case 26: return go_column_legs<float, 26>(e, parity, n_hb, n_or, st);
+        default: return hipErrorInvalidValue;
     }
 }
 
