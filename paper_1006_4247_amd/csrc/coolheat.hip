@@ -880,67 +880,91 @@ static hipError_t coolheat_round(const hsg_ensemble& e, const ChEps& ce, int i0,
 }
 
 // ---------------------------------------------------------------- split ascending pass
-// For L > 16 with few chains, each leg of pair i is spread over G workgroups, each
-// owning a slice of both sublattices, in two launches: k_ch_split_a maps the slice of
-// the leg's first sublattice (neighbours and own spins from the source configuration,
-// result into the slot's candidate buffer) and copies the slice of the other
-// sublattice; k_ch_split_b maps the second sublattice in the candidate buffer.  Each
-// leaves per-slice sums (log Jacobian, energy).  The decision of pair i is taken by
-// the cooling workgroups of pair i + 1 (every one alike, from the sums) before they
-// start, as only that leg depends on it; one of them updates the labels, counters and
-// energies, and each copies its slice of the accepted candidates over their spins.
-// The last pair is decided by k_ch_split_decide, and k_ch_split_finish advances the
-// exchange counter and the round trips.  Per chain and pair parity (pair i's sums are
-// written while pair i - 1's are read), in the scratch's partial area: ld[2][G],
-// h[2][G] and a record of both legs' slots and energies before the pair.  A slice is
-// the same range of sites h in every sublattice and component, for the maps and the
-// copies alike, so each site is copied and mapped by the workgroup that owns it.
-struct ChSplit {
-    double* ld;   // [leg][G] log Jacobian per slice (both half-steps)
-    double* hs;   // [leg][G] energy sum per slice (second half-step)
-    double* en;   // [leg] energy of the leg's configuration before the pair
-    int* slot;    // [leg] the leg's slot
+// For L > 16 with few chains.  No pair before i touches the configuration at beta_{i+1},
+// so every pair's heating leg is taken first, at once, in two launches (k_ch_heat: parity
+// 1, then parity 0), GH workgroups per leg.  What is left in order are the cooling legs:
+// two launches per pair over G workgroups per chain, each owning a slice of the sites:
+// k_ch_cool_a decides pair i - 1 (every workgroup alike, its first wave from the sums)
+// and maps parity 0, k_ch_cool_b parity 1.  A configuration stays where it is: the map
+// reads it in the slot's spins or in the slot's candidate and writes the other of the two,
+// which an accepted pair makes the configuration; so no launch copies, and k_ch_settle
+// decides the last pair and copies, once per slot, what ended in a candidate.
+// k_ch_split_finish advances the exchange counter and the round trips.
+//
+// What bounds it: the chain of launches, two per pair, each a round trip to memory for
+// the sums, one for the configuration and the site map, on 256 CUs with one or two sites
+// per thread; the couplings are asked for before the decision, as they do not depend on it.
+// Workgroups of 256 threads, as many as give a launch 512 of them and each a site per
+// thread.  Binary32 L = 32, 8 x 2 chains x 43 temperatures: 7.4 and 5.6 us per pair, 117 us
+// per half of the heating legs (0.4 GB, near the rate of HBM) and 83 us for the copies:
+// 0.86 ms a pass, against 1.39 ms with both legs of a pair (22.8 + 10.1 us) in order.
+//
+// In the scratch's partial area, per chain: the heating legs' records of all pairs, and
+// the cooling legs' of two pairs in turn (pair i's are written while pair i - 1's are read).
+constexpr int kChSlices = 64;  // at most, per leg: a lane each in the decision
+
+struct ChHeat {  // the heating leg of a pair
+    double* ld;   // [GH] log Jacobian per slice (both half-steps)
+    double* hs;   // [GH] energy sum per slice
+    double* en;   // energy of the configuration before the pair
+    double* logu; // the decision's uniform
+    int* slot;
+};
+struct ChCool {  // the cooling leg of a pair
+    double* ld;   // [G]
+    double* hs;   // [G]
+    double* en;
+    int* slot;
+    int* sel;     // the configuration is in the slot's spins (0) or candidate (1)
+};
+struct ChGroups {
+    int G, GH;
 };
 
-__device__ __forceinline__ ChSplit ch_split(const hsg_ensemble& e, int ch, int G, int i) {
+__device__ __forceinline__ double* ch_records(const hsg_ensemble& e, int ch) {
     const ScratchLayout sl = scratch_layout(e);
-    double* base = reinterpret_cast<double*>(static_cast<unsigned char*>(e.scratch) + sl.partial) +
-                   (static_cast<size_t>(ch) * 2 + (i & 1)) * (4 * G + 3);
-    ChSplit c;
-    c.ld = base;
-    c.hs = base + 2 * G;
-    c.en = base + 4 * G;
-    c.slot = reinterpret_cast<int*>(base + 4 * G + 2);
-    return c;
+    return reinterpret_cast<double*>(static_cast<unsigned char*>(e.scratch) + sl.partial) +
+           static_cast<size_t>(ch) * e.n_temps * sl.max_tiles;
+}
+__device__ __forceinline__ ChHeat ch_heat(const hsg_ensemble& e, int ch, ChGroups gr, int i) {
+    double* base = ch_records(e, ch) + static_cast<size_t>(i) * (2 * gr.GH + 3);
+    return ChHeat{base, base + gr.GH, base + 2 * gr.GH, base + 2 * gr.GH + 1, reinterpret_cast<int*>(base + 2 * gr.GH + 2)};
+}
+__device__ __forceinline__ ChCool ch_cool(const hsg_ensemble& e, int ch, ChGroups gr, int i) {
+    double* base = ch_records(e, ch) + static_cast<size_t>(e.n_temps - 1) * (2 * gr.GH + 3) + (i & 1) * (2 * gr.G + 2);
+    int* const rec = reinterpret_cast<int*>(base + 2 * gr.G + 1);
+    return ChCool{base, base + gr.G, base + 2 * gr.G, rec, rec + 1};
 }
 
 // Pair i's acceptance from the records and sums (read-only while it is evaluated):
 // ln A = b1 H(x) + b2 H(y) - b1 H(C^-1 y) - b2 H(C x) + ln det J(x) - ln det J(C^-1 y).
 struct ChDecision {
-    bool ok;
-    int x, y;
-    double ld0, ld1, hx, hy;
+    double ld0, ld1, hx, hy, en_y;
+    int ok, x, y, sel;
 };
 
-__device__ __forceinline__ ChDecision ch_split_decision(const hsg_ensemble& e, int ch, int i, int G,
-                                                        const ChSplit& c) {
+// By one wave (the result is valid in its first lane).
+__device__ __forceinline__ ChDecision ch_decide(const hsg_ensemble& e, int ch, int i, ChGroups gr) {
+    const ChCool c = ch_cool(e, ch, gr, i);
+    const ChHeat h = ch_heat(e, ch, gr, i);
+    const int lane = static_cast<int>(threadIdx.x) & 63;
+    double v[4];
+    v[0] = lane < gr.G ? c.ld[lane] : 0.0;
+    v[1] = lane < gr.GH ? h.ld[lane] : 0.0;
+    v[2] = lane < gr.G ? c.hs[lane] : 0.0;
+    v[3] = lane < gr.GH ? h.hs[lane] : 0.0;
+    const double en_x = *c.en, b1 = e.betas[i], b2 = e.betas[i + 1], logu = *h.logu;
     ChDecision d;
-    d.x = c.slot[0];
-    d.y = c.slot[1];
-    d.ld0 = d.ld1 = d.hx = d.hy = 0.0;
-    for (int g = 0; g < G; ++g) {
-        d.ld0 += c.ld[g];
-        d.ld1 += c.ld[G + g];
-        d.hx += c.hs[g];
-        d.hy += c.hs[G + g];
-    }
-    d.hx = -d.hx;  // H(C x) and H(C^-1 y)
-    d.hy = -d.hy;
-    const double b1 = e.betas[i], b2 = e.betas[i + 1];
-    const double lnA = b1 * c.en[0] + b2 * c.en[1] - b1 * d.hy - b2 * d.hx + d.ld0 - d.ld1;
-    const Words w = philox(static_cast<uint32_t>(i), e.swap_ctr[ch], e.chain_base + static_cast<uint32_t>(ch),
-                           kTagSwap << 24, key_lo(e.seed), key_hi(e.seed));
-    d.ok = log(u01_52(w.w0, w.w1)) < lnA;
+    d.en_y = *h.en;
+    d.x = *c.slot;
+    d.y = *h.slot;
+    d.sel = *c.sel;
+    d.ld0 = wave_sum(v[0]);
+    d.ld1 = wave_sum(v[1]);
+    d.hx = -wave_sum(v[2]);  // H(C x) and H(C^-1 y)
+    d.hy = -wave_sum(v[3]);
+    const double lnA = b1 * en_x + b2 * d.en_y - b1 * d.hy - b2 * d.hx + d.ld0 - d.ld1;
+    d.ok = logu < lnA ? 1 : 0;
     return d;
 }
 
@@ -967,154 +991,233 @@ __device__ __forceinline__ void ch_split_commit(const hsg_ensemble& e, int ch, i
     }
 }
 
-// Slice [h0, h1) of every sublattice and component of candidate `slot` over its spins.
 template <typename T>
-__device__ __forceinline__ void ch_split_copy(const hsg_ensemble& e, size_t slot, int N, int h0, int h1) {
-    const ScratchLayout sl = scratch_layout(e);
-    const int NH = N / 2;
-    const T* src = reinterpret_cast<const T*>(static_cast<unsigned char*>(e.scratch) + sl.cand) + slot * 3 * N;
-    T* dst = static_cast<T*>(e.spins) + slot * 3 * N;
-    for (int plane = 0; plane < 6; ++plane)
-        for (int h = h0 + static_cast<int>(threadIdx.x); h < h1; h += kChThreads)
-            dst[plane * NH + h] = src[plane * NH + h];
-}
+struct ChPlaces {
+    const T* nbr;  // the configuration whose other sublattice makes the fields
+    const T* own;  // ... whose spins are mapped
+    T* out;        // (never the element of `own`, nor a sublattice read from `nbr`)
+};
 
-// One half-step of a leg over sites [h0, h1) of sublattice p: fields from `nbr`, own
-// spins from `own`, results into `out` (may equal `own`); returns the log Jacobians'
-// sum and adds s'.S to *en if `want`.
-template <typename T, bool HEAT>
-__device__ __forceinline__ double ch_split_half(const T* nbr, const T* own, T* out, const T* __restrict__ J, int L,
-                                                int p, int h0, int h1, T eps, bool want, double* en) {
+// One half-step of a leg over sites [h0, h1) of sublattice p; `places` is called, by every
+// thread, once the first sites' couplings are asked for.  Returns the log Jacobians' sum;
+// adds s'.S to *en if `want`.
+template <typename T, bool HEAT, class Places>
+__device__ __forceinline__ double ch_half(const T* __restrict__ J, int L, int p, int h0, int h1, T eps, bool want,
+                                          double* en, Places places) {
+    constexpr int U = 2;  // sites of a thread in flight
     const int NH = L * L * L / 2;
-    const T* o0 = nbr + (0 * 2 + (1 - p)) * NH;
-    const T* o1 = nbr + (1 * 2 + (1 - p)) * NH;
-    const T* o2 = nbr + (2 * 2 + (1 - p)) * NH;
-    double ld = 0.0;
-    for (int h = h0 + static_cast<int>(threadIdx.x); h < h1; h += kChThreads) {
-        const Nbr nb = neighbours<0>(h, p, L);
-        T Sx = T(0), Sy = T(0), Sz = T(0);
+    Nbr nb[U];
+    T j[U][6];
+    const auto couplings = [&](int hb) {
 #pragma unroll
-        for (int d = 0; d < 6; ++d) {
-            const int mu = d >> 1;
-            const T jj = (d & 1) ? J[(mu * 2 + (1 - p)) * NH + nb.n[d]] : J[(mu * 2 + p) * NH + h];
-            const int idx = nb.n[d];
-            Sx = fma(jj, o0[idx], Sx);
-            Sy = fma(jj, o1[idx], Sy);
-            Sz = fma(jj, o2[idx], Sz);
+        for (int u = 0; u < U; ++u) {
+            const int h = hb + u * kChThreads < h1 ? hb + u * kChThreads : h1 - 1;
+            nb[u] = neighbours<0>(h, p, L);
+#pragma unroll
+            for (int d = 0; d < 6; ++d)
+                j[u][d] = (d & 1) ? J[((d >> 1) * 2 + (1 - p)) * NH + nb[u].n[d]] : J[((d >> 1) * 2 + p) * NH + h];
         }
-        T sx = own[(0 * 2 + p) * NH + h], sy = own[(1 * 2 + p) * NH + h], sz = own[(2 * 2 + p) * NH + h];
-        ld += coolheat_site<T, HEAT>(sx, sy, sz, Sx, Sy, Sz, eps);
-        out[(0 * 2 + p) * NH + h] = sx;
-        out[(1 * 2 + p) * NH + h] = sy;
-        out[(2 * 2 + p) * NH + h] = sz;
-        if (want) {
-            const double dx = sx, dy = sy, dz = sz;
-            *en += fma(dz, static_cast<double>(Sz), fma(dy, static_cast<double>(Sy), dx * static_cast<double>(Sx)));
+    };
+    int hb = h0 + static_cast<int>(threadIdx.x);
+    couplings(hb);
+    const ChPlaces<T> at = places();
+    const T* __restrict__ nbr = at.nbr + (1 - p) * NH;
+    const T* __restrict__ own = at.own + p * NH;
+    T* __restrict__ out = at.out + p * NH;
+    double ld = 0.0;
+    while (hb < h1) {
+        T o[U][6][3], s[U][3];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int h = hb + u * kChThreads < h1 ? hb + u * kChThreads : h1 - 1;
+#pragma unroll
+            for (int mu = 0; mu < 3; ++mu) {
+                s[u][mu] = own[mu * 2 * NH + h];
+#pragma unroll
+                for (int d = 0; d < 6; ++d) o[u][d][mu] = nbr[mu * 2 * NH + nb[u].n[d]];
+            }
         }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            T S[3] = {T(0), T(0), T(0)};
+#pragma unroll
+            for (int d = 0; d < 6; ++d)
+#pragma unroll
+                for (int mu = 0; mu < 3; ++mu) S[mu] = fma(j[u][d], o[u][d][mu], S[mu]);
+            const int h = hb + u * kChThreads;
+            if (h < h1) {
+                ld += coolheat_site<T, HEAT>(s[u][0], s[u][1], s[u][2], S[0], S[1], S[2], eps);
+#pragma unroll
+                for (int mu = 0; mu < 3; ++mu) out[mu * 2 * NH + h] = s[u][mu];
+                if (want) {
+                    const double dx = s[u][0], dy = s[u][1], dz = s[u][2];
+                    *en += fma(dz, static_cast<double>(S[2]),
+                               fma(dy, static_cast<double>(S[1]), dx * static_cast<double>(S[0])));
+                }
+            }
+        }
+        hb += U * kChThreads;
+        if (hb < h1) couplings(hb);
     }
     return ld;
 }
 
-// Workgroup (chain, leg, slice g) of pair i's first launch.
-template <typename T>
-__global__ void __launch_bounds__(kChThreads) k_ch_split_a(hsg_ensemble e, ChEps ce, int i, int G) {
-    __shared__ double red[kChThreads / 64];
-    const T eps = ch_eps<T>(ce, i);
-    const int L = e.L, N = L * L * L, NH = N / 2, R = e.n_temps;
-    const int b = xcd_order(static_cast<int>(blockIdx.x), static_cast<int>(gridDim.x));  // a chain's slices on one XCD
-    const int g = b % G, leg = (b / G) & 1, ch = b / (2 * G);
-    const ChSplit c = ch_split(e, ch, G, i);
-    const ScratchLayout sl = scratch_layout(e);
-    T* cand = reinterpret_cast<T*>(static_cast<unsigned char*>(e.scratch) + sl.cand);
-    T* spins = static_cast<T*>(e.spins);
-    const int h0 = static_cast<int>(static_cast<long long>(NH) * g / G);
-    const int h1 = static_cast<int>(static_cast<long long>(NH) * (g + 1) / G);
-    int slot;
-    double en_before;
-    bool from_cand = false;
-    if (leg == 0 && i > 0) {  // decide pair i - 1 first (uniform over the workgroup)
-        const ChSplit cp = ch_split(e, ch, G, i - 1);
-        const ChDecision d = ch_split_decision(e, ch, i - 1, G, cp);
-        if (d.ok) {  // its candidates become the spins of their slots, this slice here
-            ch_split_copy<T>(e, static_cast<size_t>(ch) * R + d.x, N, h0, h1);
-            ch_split_copy<T>(e, static_cast<size_t>(ch) * R + d.y, N, h0, h1);
-            __syncthreads();  // C x of this slice is saved before the map overwrites it
-        }
-        slot = d.ok ? d.x : cp.slot[1];
-        en_before = d.ok ? d.hx : cp.en[1];
-        from_cand = d.ok;
-        if (g == 0 && threadIdx.x == 0) ch_split_commit(e, ch, i - 1, d);
-    } else {
-        slot = label(e.slot_of_temp[ch * R + i + leg], R, e.guard);
-        en_before = e.energy[static_cast<size_t>(ch) * R + slot];
-    }
-    const size_t gs = static_cast<size_t>(ch) * R + slot;
-    const T* src = (from_cand ? cand : spins) + gs * 3 * N;
-    T* dst = cand + gs * 3 * N;
-    const T* __restrict__ J = static_cast<const T*>(e.couplings) + static_cast<size_t>(ch / e.n_chains) * 3 * N;
-    const int p = leg;  // cooling maps sublattice 0 first, heating sublattice 1
-    double unused = 0.0;
-    const double ld = leg ? ch_split_half<T, true>(src, src, dst, J, L, p, h0, h1, eps, false, &unused)
-                          : ch_split_half<T, false>(src, src, dst, J, L, p, h0, h1, eps, false, &unused);
-    if (!from_cand) {  // the slice of the other sublattice into the candidate buffer
-        const int q = 1 - p;
-        for (int mu = 0; mu < 3; ++mu)
-            for (int h = h0 + static_cast<int>(threadIdx.x); h < h1; h += kChThreads)
-                dst[(mu * 2 + q) * NH + h] = src[(mu * 2 + q) * NH + h];
-    }
-    const double LD = block_sum<kChThreads>(ld, red);
-    if (threadIdx.x == 0) {
-        c.ld[leg * G + g] = LD;
-        if (g == 0) {
-            c.slot[leg] = slot;
-            c.en[leg] = en_before;
-        }
-    }
+// Slice g of n of a sublattice's sites.
+__device__ __forceinline__ int ch_slice(int NH, int g, int n) {
+    return static_cast<int>(static_cast<long long>(NH) * g / n);
 }
 
-// Workgroup (chain, leg, slice g) of pair i's second launch.
-template <typename T>
-__global__ void __launch_bounds__(kChThreads) k_ch_split_b(hsg_ensemble e, ChEps ce, int i, int G) {
+// Workgroup (chain, pair, slice g) of the heating legs' first (STEP 0) or second half.
+template <typename T, int STEP>
+__global__ void __launch_bounds__(kChThreads) k_ch_heat(hsg_ensemble e, ChEps ce, ChGroups gr) {
     __shared__ double red[kChThreads / 64];
-    const T eps = ch_eps<T>(ce, i);
     const int L = e.L, N = L * L * L, NH = N / 2, R = e.n_temps;
-    const int b = xcd_order(static_cast<int>(blockIdx.x), static_cast<int>(gridDim.x));  // a chain's slices on one XCD
-    const int g = b % G, leg = (b / G) & 1, ch = b / (2 * G);
-    const ChSplit c = ch_split(e, ch, G, i);
+    const int b = xcd_order(static_cast<int>(blockIdx.x), static_cast<int>(gridDim.x));
+    const int g = b % gr.GH, i = b / gr.GH % (R - 1), ch = b / (gr.GH * (R - 1));
+    const T eps = ch_eps<T>(ce, i);
+    const ChHeat c = ch_heat(e, ch, gr, i);
     const ScratchLayout sl = scratch_layout(e);
-    T* dst = reinterpret_cast<T*>(static_cast<unsigned char*>(e.scratch) + sl.cand) +
-             (static_cast<size_t>(ch) * R + c.slot[leg]) * 3 * N;
+    unsigned char* scr = static_cast<unsigned char*>(e.scratch);
+    const size_t gs = static_cast<size_t>(ch) * R + label(e.slot_of_temp[ch * R + i + 1], R, e.guard);
+    T* cand = reinterpret_cast<T*>(scr + sl.cand) + gs * 3 * N;
+    const T* spins = static_cast<const T*>(e.spins) + gs * 3 * N;
     const T* __restrict__ J = static_cast<const T*>(e.couplings) + static_cast<size_t>(ch / e.n_chains) * 3 * N;
-    const int p = 1 - leg;
-    const int h0 = static_cast<int>(static_cast<long long>(NH) * g / G);
-    const int h1 = static_cast<int>(static_cast<long long>(NH) * (g + 1) / G);
     double en = 0.0;
-    const double ld = leg ? ch_split_half<T, true>(dst, dst, dst, J, L, p, h0, h1, eps, true, &en)
-                          : ch_split_half<T, false>(dst, dst, dst, J, L, p, h0, h1, eps, true, &en);
+    const double ld = ch_half<T, true>(J, L, 1 - STEP, ch_slice(NH, g, gr.GH), ch_slice(NH, g + 1, gr.GH), eps, STEP == 1,
+                                       &en, [&] { return ChPlaces<T>{STEP ? cand : spins, spins, cand}; });
     const double LD = block_sum<kChThreads>(ld, red);
-    const double EN = block_sum<kChThreads>(en, red);
+    if constexpr (STEP == 1) en = block_sum<kChThreads>(en, red);
     if (threadIdx.x == 0) {
-        c.ld[leg * G + g] += LD;
-        c.hs[leg * G + g] = EN;
+        if constexpr (STEP == 0) {
+            c.ld[g] = LD;
+            if (g == 0) {
+                int* in_cand = reinterpret_cast<int*>(scr + sl.flags);
+                *c.en = e.energy[gs];
+                *c.slot = static_cast<int>(gs - static_cast<size_t>(ch) * R);
+                const Words w = philox(static_cast<uint32_t>(i), e.swap_ctr[ch], e.chain_base + static_cast<uint32_t>(ch),
+                                       kTagSwap << 24, key_lo(e.seed), key_hi(e.seed));
+                *c.logu = log(u01_52(w.w0, w.w1));
+                in_cand[gs] = 0;
+                if (i == 0) in_cand[static_cast<size_t>(ch) * R + label(e.slot_of_temp[ch * R], R, e.guard)] = 0;
+            }
+        } else {
+            c.ld[g] += LD;
+            c.hs[g] = en;
+        }
     }
 }
 
-// The last pair: decision, slice-wise copy of accepted candidates, commit.
+// Workgroup (chain, slice g) of pair i's cooling leg, parity 0.
 template <typename T>
-__global__ void __launch_bounds__(kChThreads) k_ch_split_decide(hsg_ensemble e, int i, int G) {
-    const int N = e.L * e.L * e.L, R = e.n_temps;
+__global__ void __launch_bounds__(kChThreads) k_ch_cool_a(hsg_ensemble e, ChEps ce, int i, ChGroups gr) {
+    __shared__ double red[kChThreads / 64];
+    __shared__ ChDecision s_dec;
+    const T eps = ch_eps<T>(ce, i);
+    const int L = e.L, N = L * L * L, NH = N / 2, R = e.n_temps;
     const int b = xcd_order(static_cast<int>(blockIdx.x), static_cast<int>(gridDim.x));  // a chain's slices on one XCD
-    const int g = b % G, ch = b / G;
-    const ChSplit c = ch_split(e, ch, G, i);
-    const ChDecision d = ch_split_decision(e, ch, i, G, c);
-    if (d.ok) {
-        const int NH = N / 2;
-        const int h0 = static_cast<int>(static_cast<long long>(NH) * g / G);
-        const int h1 = static_cast<int>(static_cast<long long>(NH) * (g + 1) / G);
-        ch_split_copy<T>(e, static_cast<size_t>(ch) * R + d.x, N, h0, h1);
-        ch_split_copy<T>(e, static_cast<size_t>(ch) * R + d.y, N, h0, h1);
+    const int g = b % gr.G, ch = b / gr.G;
+    const ChCool c = ch_cool(e, ch, gr, i);
+    const ScratchLayout sl = scratch_layout(e);
+    unsigned char* scr = static_cast<unsigned char*>(e.scratch);
+    const T* __restrict__ J = static_cast<const T*>(e.couplings) + static_cast<size_t>(ch / e.n_chains) * 3 * N;
+    double unused = 0.0;
+    const double ld = ch_half<T, false>(J, L, 0, ch_slice(NH, g, gr.G), ch_slice(NH, g + 1, gr.G), eps, false, &unused, [&] {
+        int slot, sel = 0;
+        double en;
+        if (i > 0) {
+            if (threadIdx.x < 64) {
+                const ChDecision d = ch_decide(e, ch, i - 1, gr);
+                if (threadIdx.x == 0) s_dec = d;
+            }
+            lds_barrier();
+            const ChDecision d = s_dec;
+            slot = d.ok ? d.x : d.y;
+            if (d.ok) sel = 1 - d.sel;
+            en = d.ok ? d.hx : d.en_y;
+            if (g == 0 && threadIdx.x == 0) {
+                ch_split_commit(e, ch, i - 1, d);
+                if (d.ok) {
+                    int* in_cand = reinterpret_cast<int*>(scr + sl.flags) + static_cast<size_t>(ch) * R;
+                    in_cand[d.x] = sel;
+                    in_cand[d.y] = 1;
+                }
+            }
+        } else {
+            slot = label(e.slot_of_temp[ch * R], R, e.guard);
+            en = e.energy[static_cast<size_t>(ch) * R + slot];
+        }
+        if (g == 0 && threadIdx.x == 0) {
+            *c.slot = slot;
+            *c.sel = sel;
+            *c.en = en;
+        }
+        const size_t at = (static_cast<size_t>(ch) * R + slot) * 3 * N;
+        T* cand = reinterpret_cast<T*>(scr + sl.cand) + at;
+        T* spins = static_cast<T*>(e.spins) + at;
+        const T* src = sel ? cand : spins;
+        return ChPlaces<T>{src, src, sel ? spins : cand};
+    });
+    const double LD = block_sum<kChThreads, true>(ld, red);
+    if (threadIdx.x == 0) c.ld[g] = LD;
+}
+
+// ... and parity 1.
+template <typename T>
+__global__ void __launch_bounds__(kChThreads) k_ch_cool_b(hsg_ensemble e, ChEps ce, int i, ChGroups gr) {
+    __shared__ double red[kChThreads / 64];
+    const T eps = ch_eps<T>(ce, i);
+    const int L = e.L, N = L * L * L, NH = N / 2, R = e.n_temps;
+    const int b = xcd_order(static_cast<int>(blockIdx.x), static_cast<int>(gridDim.x));  // a chain's slices on one XCD
+    const int g = b % gr.G, ch = b / gr.G;
+    const ChCool c = ch_cool(e, ch, gr, i);
+    const ScratchLayout sl = scratch_layout(e);
+    const T* __restrict__ J = static_cast<const T*>(e.couplings) + static_cast<size_t>(ch / e.n_chains) * 3 * N;
+    double en = 0.0;
+    const double ld = ch_half<T, false>(J, L, 1, ch_slice(NH, g, gr.G), ch_slice(NH, g + 1, gr.G), eps, true, &en, [&] {
+        const size_t at = (static_cast<size_t>(ch) * R + *c.slot) * 3 * N;
+        T* cand = reinterpret_cast<T*>(static_cast<unsigned char*>(e.scratch) + sl.cand) + at;
+        T* spins = static_cast<T*>(e.spins) + at;
+        T* out = *c.sel ? spins : cand;
+        return ChPlaces<T>{out, *c.sel ? cand : spins, out};
+    });
+    const double ld_before = threadIdx.x == 0 ? c.ld[g] : 0.0;
+    const double LD = block_sum<kChThreads, true>(ld, red);
+    const double EN = block_sum<kChThreads, true>(en, red);
+    if (threadIdx.x == 0) {
+        c.ld[g] = ld_before + LD;
+        c.hs[g] = EN;
     }
-    if (g == 0 && threadIdx.x == 0) ch_split_commit(e, ch, i, d);
+}
+
+// The last pair's decision and commit; candidates that became configurations over their
+// spins.  Workgroup (chain, slot, part).
+constexpr int kChSettle = 8192;  // elements per part
+template <typename T>
+__global__ void __launch_bounds__(kChThreads) k_ch_settle(hsg_ensemble e, ChGroups gr, int parts) {
+    __shared__ ChDecision s_dec;
+    const int n = 3 * e.L * e.L * e.L, R = e.n_temps, i = R - 2;
+    const int part = static_cast<int>(blockIdx.x) % parts, r = static_cast<int>(blockIdx.x) / parts % R;
+    const int ch = static_cast<int>(blockIdx.x) / (parts * R);
+    const ScratchLayout sl = scratch_layout(e);
+    unsigned char* scr = static_cast<unsigned char*>(e.scratch);
+    const size_t gs = static_cast<size_t>(ch) * R + r;
+    int in_cand = reinterpret_cast<const int*>(scr + sl.flags)[gs];
+    if (r == *ch_cool(e, ch, gr, i).slot || r == *ch_heat(e, ch, gr, i).slot) {
+        if (threadIdx.x < 64) {
+            const ChDecision d = ch_decide(e, ch, i, gr);
+            if (threadIdx.x == 0) s_dec = d;
+        }
+        __syncthreads();
+        const ChDecision d = s_dec;
+        if (d.ok) in_cand = r == d.x ? 1 - d.sel : 1;
+        if (r == d.x && part == 0 && threadIdx.x == 0) ch_split_commit(e, ch, i, d);
+    }
+    if (!in_cand) return;
+    const T* __restrict__ src = reinterpret_cast<const T*>(scr + sl.cand) + gs * n;
+    T* __restrict__ dst = static_cast<T*>(e.spins) + gs * n;
+    const int end = (part + 1) * kChSettle < n ? (part + 1) * kChSettle : n;
+#pragma unroll 4
+    for (int k = part * kChSettle + static_cast<int>(threadIdx.x); k < end; k += kChThreads) dst[k] = src[k];
 }
 
 // Per chain, after the pass: exchange counter and round trips.
@@ -1139,30 +1242,42 @@ __global__ void k_ch_split_finish(hsg_ensemble e) {
     }
 }
 
-// Workgroups per leg for the split pass (L > 16): about 512 workgroups per launch, at
-// least 512 sites per slice, within the scratch's partial area; 1 = not split.
-static int ch_split_groups(const hsg_ensemble& e) {
-    if (e.L <= 16) return 1;
-    const int chains = e.n_samples * e.n_chains;
-    const long long NH = static_cast<long long>(e.L) * e.L * e.L / 2;
+// Workgroups per leg for the split pass (L > 16): cooling about 512 per launch, a site per
+// thread at least; heating up to eight of 2048 sites; both within the scratch's partial
+// area.  G = 1: not split.
+static ChGroups ch_split_groups(const hsg_ensemble& e) {
+    if (e.L <= 16) return {1, 1};
+    const int chains = e.n_samples * e.n_chains, R = e.n_temps;
+    const int NH = e.L * e.L * e.L / 2;
     const ScratchLayout sl = scratch_layout(e);
-    const long long per_chain = static_cast<long long>(e.n_temps) * sl.max_tiles;  // doubles
-    long long G = (256 + chains - 1) / chains;
-    G = G < NH / 512 ? G : NH / 512;
-    G = G < (per_chain / 2 - 3) / 4 ? G : (per_chain / 2 - 3) / 4;  // two pair parities
-    return G < 2 ? 1 : static_cast<int>(G);
+    const long long per_chain = static_cast<long long>(R) * sl.max_tiles;  // doubles
+    if (chains >= 256) return {1, 1};
+    ChGroups gr;
+    gr.GH = NH / 2048 < 1 ? 1 : NH / 2048 < 8 ? NH / 2048 : 8;
+    while (gr.GH > 1 && 2 * static_cast<long long>(R - 1) * (2 * gr.GH + 3) > per_chain) --gr.GH;
+    long long G = (512 + chains - 1) / chains;
+    const long long room = ((per_chain - static_cast<long long>(R - 1) * (2 * gr.GH + 3)) / 2 - 2) / 2;
+    G = G < NH / kChThreads ? G : NH / kChThreads;
+    G = G < kChSlices ? G : kChSlices;
+    G = G < room ? G : room;
+    gr.G = G < 2 ? 1 : static_cast<int>(G);
+    return gr;
 }
 
 template <typename T>
-static hipError_t coolheat_split_pass(const hsg_ensemble& e, const ChEps& ce, int G, hipStream_t st) {
+static hipError_t coolheat_split_pass(const hsg_ensemble& e, const ChEps& ce, ChGroups gr, hipStream_t st) {
     const int chains = e.n_samples * e.n_chains, R = e.n_temps;
+    const dim3 heat(static_cast<unsigned>(chains) * (R - 1) * gr.GH), cool(chains * gr.G), nt(kChThreads);
+    hipLaunchKernelGGL((k_ch_heat<T, 0>), heat, nt, 0, st, e, ce, gr);
+    hipLaunchKernelGGL((k_ch_heat<T, 1>), heat, nt, 0, st, e, ce, gr);
     for (int i = 0; i < R - 1; ++i) {
-        hipLaunchKernelGGL(k_ch_split_a<T>, dim3(chains * 2 * G), dim3(kChThreads), 0, st, e, ce, i, G);
-        hipLaunchKernelGGL(k_ch_split_b<T>, dim3(chains * 2 * G), dim3(kChThreads), 0, st, e, ce, i, G);
+        hipLaunchKernelGGL(k_ch_cool_a<T>, cool, nt, 0, st, e, ce, i, gr);
+        hipLaunchKernelGGL(k_ch_cool_b<T>, cool, nt, 0, st, e, ce, i, gr);
         const hipError_t err = hipGetLastError();
         if (err != hipSuccess) return err;
     }
-    hipLaunchKernelGGL(k_ch_split_decide<T>, dim3(chains * G), dim3(kChThreads), 0, st, e, R - 2, G);
+    const int parts = (3 * e.L * e.L * e.L + kChSettle - 1) / kChSettle;
+    hipLaunchKernelGGL(k_ch_settle<T>, dim3(static_cast<unsigned>(chains) * R * parts), nt, 0, st, e, gr, parts);
     const long long n_fin = static_cast<long long>(chains) * R;
     hipLaunchKernelGGL(k_ch_split_finish, dim3(static_cast<unsigned>((n_fin + 255) / 256)), dim3(256), 0, st, e);
     return hipGetLastError();
@@ -1208,10 +1323,10 @@ hipError_t launch_coolheat(const hsg_ensemble& e, int pairing, double eps, const
     if (e.n_samples * e.n_chains <= 0 || R < 2) return hipSuccess;
     if (pairing == 0) {
         // ascending order: each pair sees the states the previous pair left
-        const int G = ch_split_groups(e);
-        if (G > 1)
-            return e.precision == HSG_FP64 ? coolheat_split_pass<double>(e, ce, G, st)
-                                           : coolheat_split_pass<float>(e, ce, G, st);
+        const ChGroups gr = ch_split_groups(e);
+        if (gr.G > 1)
+            return e.precision == HSG_FP64 ? coolheat_split_pass<double>(e, ce, gr, st)
+                                           : coolheat_split_pass<float>(e, ce, gr, st);
         if (e.precision == HSG_FP32 && e.L <= 16) {
             const hipError_t err = coolheat_asc_two(e, ce, st);
             if (err != hipErrorNotSupported) return err;
