@@ -821,6 +821,269 @@ __global__ void __launch_bounds__(kDecThreads) k_dec_split_apply(hsg_ensemble e,
     }
 }
 
+// ---------------------------------------------------------------- one launch per pair
+// Where the launches, not the sites, take the time of the split pass (few chains): pair
+// i of every chain is spread over G workgroups, each owning a slice of the decimated
+// sublattice, in one launch.  It decides pair i - 1 (from the per-slice sums, every
+// workgroup alike) and then, from the fields it needs for pair i's terms anyway, draws the
+// re-inserted spins of both configurations before the pair is decided.  They go to the
+// sublattice's other place: each sublattice of a slot is in its spins or in its candidate,
+// a pair writes the one it is not in, and an accepted pair turns the two over, so nothing
+// is copied until k_dec_settle decides the last pair and brings what ended in a candidate
+// back.
+//
+// What bounds it: in one launch, three round trips to memory one after the other (the
+// sums, x's configuration, the new sums) and one site's arithmetic; what does not depend
+// on the decision (couplings, y's configuration and draws) does not wait for it.  Binary32
+// L = 24, 8 x 2 chains x 27 temperatures, 1 pair in 3 accepted: 8.4 us a pair, against
+// 16.2 us in two launches; L = 18: 8.0 against 15.5 us.
+//
+// In the scratch's partial area, per chain and pair parity (pair i's record is written
+// while pair i - 1's is read): three sums per slice and the record.
+constexpr int kDecSlices = 64;  // at most: a lane each in the decision
+
+struct DecPair {
+    double* sum;   // [3][G]: ln A, s.S of x's and y's new spins
+    double* logu;  // the decision's uniform
+    int* rec;      // x, y, x's sublattices in the candidate (bit p)
+};
+
+__device__ __forceinline__ DecPair dec_pair(const hsg_ensemble& e, int ch, int G, int i) {
+    const ScratchLayout sl = scratch_layout(e);
+    double* base = reinterpret_cast<double*>(static_cast<unsigned char*>(e.scratch) + sl.partial) +
+                   (static_cast<size_t>(ch) * 2 + (i & 1)) * (3 * G + 3);
+    return DecPair{base, base + 3 * G, reinterpret_cast<int*>(base + 3 * G + 1)};
+}
+
+__device__ __forceinline__ int dec_role(const hsg_ensemble& e, int ch, uint32_t n, int i) {
+    return (static_cast<int>(philox(0u, n, e.chain_base + static_cast<uint32_t>(ch), kTagDecimateRole << 24, key_lo(e.seed),
+                                    key_hi(e.seed)).w0 & 1u) + i) & 1;
+}
+
+struct DecDecision {
+    double lnA, ex, ey;
+    int ok, x, y, loc;
+};
+
+// Pair i's decision by one wave (the result is valid in its first lane).
+__device__ __forceinline__ DecDecision dec_decide(const DecPair& s, int G) {
+    const int lane = static_cast<int>(threadIdx.x) & 63;
+    double v[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) v[k] = lane < G ? s.sum[k * G + lane] : 0.0;
+    const double logu = *s.logu;
+    DecDecision d;
+    d.x = s.rec[0];
+    d.y = s.rec[1];
+    d.loc = s.rec[2];
+    d.lnA = wave_sum(v[0]);
+    d.ex = wave_sum(v[1]);
+    d.ey = wave_sum(v[2]);
+    d.ok = logu < d.lnA ? 1 : 0;
+    return d;
+}
+
+// Labels, counters, energies and diagnostics of pair i, which decimated sublattice p (one
+// thread); the places of the sublattices of both slots.
+__device__ __forceinline__ void dec_commit(const hsg_ensemble& e, int ch, int i, int p, const DecDecision& d, int* in_cand) {
+    const int R = e.n_temps;
+    long long* st = reinterpret_cast<long long*>(e.swap_stats) + static_cast<size_t>(ch) * (R - 1) * 2;
+    if (e.work) {
+        e.work[(static_cast<size_t>(ch) * (R - 1) + i) * 2] = d.lnA;
+        e.work[(static_cast<size_t>(ch) * (R - 1) + i) * 2 + 1] = static_cast<double>(p);
+    }
+    if (!isfinite(d.lnA)) atomicOr(e.guard, 1);
+    st[2 * i] += 1;
+    if (d.ok) {
+        int* tos = e.temp_of_slot + static_cast<size_t>(ch) * R;
+        int* sot = e.slot_of_temp + static_cast<size_t>(ch) * R;
+        sot[i] = d.y;
+        sot[i + 1] = d.x;
+        tos[d.x] = i + 1;
+        tos[d.y] = i;
+        st[2 * i + 1] += 1;
+        e.energy[static_cast<size_t>(ch) * R + d.x] = -d.ex;
+        e.energy[static_cast<size_t>(ch) * R + d.y] = -d.ey;
+        if (!isfinite(d.ex) || !isfinite(d.ey)) atomicOr(e.guard, 1);
+        if (in_cand) {
+            in_cand[static_cast<size_t>(ch) * R + d.x] = d.loc ^ (1 << p);
+            in_cand[static_cast<size_t>(ch) * R + d.y] = 1 << p;
+        }
+    }
+}
+
+// Workgroup (chain, slice g) of pair i: the first half of its threads on y, the second on
+// x, a site of a configuration each.  Every wave of the second half takes the decision of
+// pair i - 1 for itself, while the first half, which does not wait for it, draws.
+template <typename T>
+__global__ void __launch_bounds__(2 * kDecThreads) k_dec_pair(hsg_ensemble e, int i, int G) {
+    constexpr int NW = kDecThreads / 64;  // waves of a half
+    __shared__ double red[3][NW];
+    __shared__ double s_norm[2][kDecThreads];
+    constexpr int HV = sizeof(T) == 4 ? 2 : 1;  // sites that share a Philox block: (q, q + N/4) in binary32
+    const int L = e.L, N = L * L * L, NH = N / 2, M = NH / HV;
+    const int R = e.n_temps, C = e.n_chains;
+    const int t = static_cast<int>(threadIdx.x) & (kDecThreads - 1);
+    const bool is_x = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x)) >= kDecThreads;
+    // a chain's slices on one XCD (they read each other's neighbouring sites)
+    const int item = xcd_order(static_cast<int>(blockIdx.x), static_cast<int>(gridDim.x));
+    const int ch = item / G, g = item % G;
+    const DecPair ds = dec_pair(e, ch, G, i);
+    const uint32_t n = e.swap_ctr[ch];
+    const uint32_t k0 = key_lo(e.seed), k1 = key_hi(e.seed);
+    const int p = dec_role(e, ch, n, i);
+    const ScratchLayout sl = scratch_layout(e);
+    unsigned char* scr = static_cast<unsigned char*>(e.scratch);
+    T* spins = static_cast<T*>(e.spins) + static_cast<size_t>(ch) * R * 3 * N;
+    T* cand = reinterpret_cast<T*>(scr + sl.cand) + static_cast<size_t>(ch) * R * 3 * N;
+    const T* __restrict__ J = static_cast<const T*>(e.couplings) + static_cast<size_t>(ch / C) * 3 * N;
+    const double b1 = e.betas[i], b2 = e.betas[i + 1];
+    const float fb1 = static_cast<float>(b1), fb2 = static_cast<float>(b2);
+    const float fr0 = static_cast<float>(b2 / b1);
+    const uint32_t c3 = (kTagDecimate << 24) | (static_cast<uint32_t>(i) & 0xFFFFu);
+    const uint32_t slot0 = e.slot_base + static_cast<uint32_t>(ch) * static_cast<uint32_t>(R);
+    const int m0 = static_cast<int>(static_cast<long long>(M) * g / G);
+    const int ns = static_cast<int>(static_cast<long long>(M) * (g + 1) / G) - m0;
+    int slot = 0, loc = 0, k = 0, m = 0, h = 0;  // loc: as DecPair's record
+    bool on = false;
+    Nbr nb;
+    T j[6];
+    const auto site = [&](int first) {  // the thread's next site and its couplings
+        on = first + t < HV * ns;
+        k = on ? first + t : 0;
+        m = m0 + (k < ns ? k : k - ns);
+        h = k < ns ? m : m + M;
+        nb = neighbours<0>(h, p, L);
+#pragma unroll
+        for (int d = 0; d < 6; ++d)
+            j[d] = (d & 1) ? J[((d >> 1) * 2 + (1 - p)) * NH + nb.n[d]] : J[((d >> 1) * 2 + p) * NH + h];
+    };
+    site(0);
+    if (is_x) {
+        int* in_cand = reinterpret_cast<int*>(scr + sl.flags);
+        const bool first = g == 0 && t == 0;
+        if (i > 0) {
+            const DecDecision d = dec_decide(dec_pair(e, ch, G, i - 1), G);
+            slot = __builtin_amdgcn_readfirstlane(d.ok ? d.x : d.y);
+            loc = __builtin_amdgcn_readfirstlane(d.ok ? d.loc ^ (1 << (1 - p)) : 0);
+            if (first) dec_commit(e, ch, i - 1, 1 - p, d, in_cand);
+        } else {
+            slot = label(e.slot_of_temp[static_cast<size_t>(ch) * R], R, e.guard);
+            if (g == 0)
+                for (int r = t; r < R; r += kDecThreads) in_cand[static_cast<size_t>(ch) * R + r] = 0;
+        }
+        if (first) {
+            ds.rec[0] = slot;
+            ds.rec[2] = loc;
+        }
+    } else {
+        // pairs before i never touch the configuration at beta_{i+1}
+        slot = label(e.slot_of_temp[static_cast<size_t>(ch) * R + i + 1], R, e.guard);
+        if (g == 0 && t == 0) {
+            const Words w = philox(static_cast<uint32_t>(i), n, e.chain_base + static_cast<uint32_t>(ch), kTagSwap << 24, k0, k1);
+            *ds.logu = log(u01_52(w.w0, w.w1));
+            ds.rec[1] = slot;
+        }
+    }
+    // parity 1 - p is read and parity p written, the latter where it is not now
+    const T* __restrict__ nbr = ((loc >> (1 - p)) & 1 ? cand : spins) + (static_cast<size_t>(slot) * 6 + (1 - p)) * NH;
+    T* __restrict__ out = ((loc >> p) & 1 ? spins : cand) + (static_cast<size_t>(slot) * 6 + p) * NH;
+    const T beta = static_cast<T>(is_x ? b2 : b1);  // where the configuration would go
+    double acc = 0.0, en = 0.0;
+    int par = 0;
+    for (int first = 0; first < HV * ns; first += kDecThreads, par ^= 1) {
+        if (first > 0) site(first);
+        T o[6][3], S[3] = {T(0), T(0), T(0)};
+#pragma unroll
+        for (int d = 0; d < 6; ++d)
+#pragma unroll
+            for (int mu = 0; mu < 3; ++mu) o[d][mu] = nbr[mu * 2 * NH + nb.n[d]];
+        const Words w = philox(static_cast<uint32_t>(m), n, slot0 + static_cast<uint32_t>(slot), c3, k0, k1);
+#pragma unroll
+        for (int d = 0; d < 6; ++d)
+#pragma unroll
+            for (int mu = 0; mu < 3; ++mu) S[mu] = fma(j[d], o[d][mu], S[mu]);
+        const double norm = norm3<T>(S[0], S[1], S[2]);
+        const auto draw = [&] {
+            if (!on) return;
+            T v[3];
+            if constexpr (sizeof(T) == 4) {
+                const bool hi = k >= ns;
+                heatbath<T>(S[0], S[1], S[2], beta, static_cast<T>(u01_23(hi ? w.w2 : w.w0)),
+                            static_cast<T>(u01_23(hi ? w.w3 : w.w1)), v[0], v[1], v[2]);
+            } else {
+                heatbath<T>(S[0], S[1], S[2], beta, static_cast<T>(u01_52(w.w0, w.w1)), static_cast<T>(u01_52(w.w2, w.w3)),
+                            v[0], v[1], v[2]);
+            }
+#pragma unroll
+            for (int mu = 0; mu < 3; ++mu) out[mu * 2 * NH + h] = v[mu];
+            const double dx = v[0], dy = v[1], dz = v[2];
+            en += fma(dz, static_cast<double>(S[2]), fma(dy, static_cast<double>(S[1]), dx * static_cast<double>(S[0])));
+        };
+        if (is_x)
+            s_norm[par][t] = norm;
+        else
+            draw();
+        lds_barrier();
+        if (is_x) {
+            draw();
+        } else if (on) {
+            const double a = s_norm[par][t], c = norm;
+            if constexpr (sizeof(T) == 4)
+                acc += fma(b2 - b1, a - c,
+                           static_cast<double>(dec_log_ratio_f(static_cast<float>(a), static_cast<float>(c), fb1, fb2, fr0)));
+            else
+                acc += (log_sinhc(b2 * a) - log_sinhc(b1 * a)) + (log_sinhc(b1 * c) - log_sinhc(b2 * c));
+        }
+    }
+    acc = wave_sum(acc);
+    en = wave_sum(en);
+    if ((t & 63) == 0) {
+        if (!is_x) red[0][t >> 6] = acc;
+        red[is_x ? 1 : 2][t >> 6] = en;
+    }
+    lds_barrier();
+    if (threadIdx.x < 3) {
+        double sum = 0.0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) sum += red[threadIdx.x][w];
+        ds.sum[static_cast<int>(threadIdx.x) * G + g] = sum;
+    }
+}
+
+// The last pair's decision and commit; sublattices that ended in a candidate over their
+// spins.  Workgroup (chain, slot, component and sublattice, part).
+constexpr int kDecSettle = 8192;  // sites per part
+template <typename T>
+__global__ void __launch_bounds__(kDecThreads) k_dec_settle(hsg_ensemble e, int G, int parts) {
+    __shared__ DecDecision s_dec;
+    const int N = e.L * e.L * e.L, NH = N / 2, R = e.n_temps, i = R - 2;
+    const int part = static_cast<int>(blockIdx.x) % parts, plane = static_cast<int>(blockIdx.x) / parts % 6;
+    const int cr = static_cast<int>(blockIdx.x) / (parts * 6), ch = cr / R, r = cr % R;
+    const ScratchLayout sl = scratch_layout(e);
+    unsigned char* scr = static_cast<unsigned char*>(e.scratch);
+    int in_cand = reinterpret_cast<const int*>(scr + sl.flags)[cr];
+    const DecPair ds = dec_pair(e, ch, G, i);
+    if (r == ds.rec[0] || r == ds.rec[1]) {
+        if (threadIdx.x < 64) {
+            const DecDecision d = dec_decide(ds, G);
+            if (threadIdx.x == 0) s_dec = d;
+        }
+        __syncthreads();
+        const DecDecision d = s_dec;
+        const int p = dec_role(e, ch, e.swap_ctr[ch], i);
+        if (d.ok) in_cand = r == d.x ? d.loc ^ (1 << p) : 1 << p;
+        if (r == d.x && plane == 0 && part == 0 && threadIdx.x == 0) dec_commit(e, ch, i, p, d, nullptr);
+    }
+    if (!((in_cand >> (plane & 1)) & 1)) return;
+    const size_t at = static_cast<size_t>(cr) * 3 * N + static_cast<size_t>(plane) * NH;
+    const T* __restrict__ src = reinterpret_cast<const T*>(scr + sl.cand) + at;
+    T* __restrict__ dst = static_cast<T*>(e.spins) + at;
+    const int end = (part + 1) * kDecSettle < NH ? (part + 1) * kDecSettle : NH;
+#pragma unroll 4
+    for (int k = part * kDecSettle + static_cast<int>(threadIdx.x); k < end; k += kDecThreads) dst[k] = src[k];
+}
+
 // After every pair: advance the exchange counter, update round trips and clear the
 // diagnostics of the pairs not attempted.  One thread per (chain, slot): thread r of
 // a chain updates slot r's round-trip state from its final temperature, clears pair r
@@ -921,6 +1184,41 @@ static int split_groups(const hsg_ensemble& e) {
     return G < 2 ? 1 : static_cast<int>(G);
 }
 
+// Workgroups per chain for one launch per pair (L > 16, scratch given): a site of each
+// configuration per thread, 64 at most, within the scratch's partial area (two pairs'
+// records); 0 = not taken.  Drawing before the decision is wasted on a rejected pair, so
+// it is for launches whose sites do not fill the chip: two launches / one, in us a pass,
+// with 1 pair in 3 and with none accepted: binary32 L = 24, 16 chains (110 592 sites) 438 /
+// 228 and 282 / 220, 64 chains 246 / 226 and 167 / 215; L = 18, 16 chains 305 / 161 and
+// 285 / 155; binary64 L = 18, 16 chains (46 656 sites) 472 / 252 and 414 / 249, L = 24, 16
+// chains 391 / 260 and 252 / 262.  (At L = 28, 8 chains: 471 / 309 and 280 / 299.)
+static int pair_groups(const hsg_ensemble& e) {
+    if (e.L <= 16 || e.scratch == nullptr) return 0;
+    const long long chains = static_cast<long long>(e.n_samples) * e.n_chains;
+    const long long NH = static_cast<long long>(e.L) * e.L * e.L / 2;
+    if (chains * NH > (e.precision == HSG_FP64 ? 1 << 16 : 1 << 17)) return 0;
+    if (NH > 2 * kDecThreads * kDecSlices) return 0;  // more than two sites of a configuration per thread
+    const ScratchLayout sl = scratch_layout(e);
+    const long long per_chain = static_cast<long long>(e.n_temps) * sl.max_tiles;  // doubles
+    long long G = NH / kDecThreads < kDecSlices ? NH / kDecThreads : kDecSlices;
+    G = G < (per_chain / 2 - 3) / 3 ? G : (per_chain / 2 - 3) / 3;
+    return G < 2 ? 0 : static_cast<int>(G);
+}
+
+template <typename T>
+static hipError_t decimate_pair_pass(const hsg_ensemble& e, int G, hipStream_t st) {
+    const int chains = e.n_samples * e.n_chains, R = e.n_temps;
+    for (int i = 0; i < R - 1; ++i) {
+        hipLaunchKernelGGL(k_dec_pair<T>, dim3(chains * G), dim3(2 * kDecThreads), 0, st, e, i, G);
+        const hipError_t err = hipGetLastError();
+        if (err != hipSuccess) return err;
+    }
+    const int parts = (e.L * e.L * e.L / 2 + kDecSettle - 1) / kDecSettle;
+    hipLaunchKernelGGL(k_dec_settle<T>, dim3(static_cast<unsigned>(chains) * R * 6 * parts), dim3(kDecThreads), 0, st, e, G,
+                       parts);
+    return hipGetLastError();
+}
+
 static unsigned finish_blocks(const hsg_ensemble& e) {
     const long long n = static_cast<long long>(e.n_samples) * e.n_chains * e.n_temps;
     return static_cast<unsigned>((n + 255) / 256);
@@ -930,6 +1228,13 @@ hipError_t launch_decimate(const hsg_ensemble& e, int pairing, hipStream_t st) {
     const int chains = e.n_samples * e.n_chains;
     const int R = e.n_temps;
     if (chains <= 0 || R < 2) return hipSuccess;
+    if (const int GP = pairing == 0 ? pair_groups(e) : 0) {
+        const hipError_t err = e.precision == HSG_FP64 ? decimate_pair_pass<double>(e, GP, st)
+                                                       : decimate_pair_pass<float>(e, GP, st);
+        if (err != hipSuccess) return err;
+        hipLaunchKernelGGL(k_decimate_finish, dim3(finish_blocks(e)), dim3(256), 0, st, e, pairing, 0);
+        return hipGetLastError();
+    }
     const int G = pairing == 0 ? split_groups(e) : 1;
     if (G > 1) {
         for (int i = 0; i < R - 1; ++i) {
