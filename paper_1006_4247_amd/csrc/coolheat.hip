@@ -20,6 +20,8 @@
 #include "hsg_device.h"
 #include "hsg_launch.h"
 
+#include <type_traits>
+
 namespace hsg {
 
 constexpr int kChThreads = 256;
@@ -175,9 +177,8 @@ __device__ __forceinline__ T ch_eps(const ChEps& c, int i) {
     return static_cast<T>(c.pair ? c.pair[i] : c.eps);
 }
 
-// LDS-resident legs (L <= 16): the replica in LDS, couplings from global memory.
-// NT threads: 256 where a launch holds many pairs, more for the single pair per
-// chain of an ascending round, whose legs then finish sooner.
+// LDS-resident legs (L <= 16) of one pair per chain: the replica in LDS, couplings from
+// global memory.
 //
 // PREV (ascending rounds i0 >= 1, one pair per chain): the cooling leg's workgroup
 // first decides pair i0 - 1 of its chain and copies that pair's accepted candidates
@@ -543,10 +544,153 @@ __global__ void k_coolheat_copyback(hsg_ensemble e, int i0, int istep, int npc) 
     for (size_t v = threadIdx.x; v < nv; v += blockDim.x) dst[v] = src[v];
 }
 
-// A call that selects no pair: only the per-chain finish.
+// Per chain, after the decisions: exchange counter, round trips and, after the even or odd
+// pairs (istep 2, from i0), zeros for the pairs not attempted.
 __global__ void k_coolheat_finish(hsg_ensemble e, int i0, int istep) {
-    const int ch = static_cast<int>(blockIdx.x * blockDim.x + threadIdx.x);
-    if (ch < e.n_samples * e.n_chains) coolheat_finish_chain(e, ch, i0, istep);
+    // one thread per (chain, slot): slot r's round-trip state from its temperature; the
+    // thread of slot 0 advances the chain's counter
+    const int n_chains = e.n_samples * e.n_chains;
+    const int R = e.n_temps;
+    const long long b = static_cast<long long>(blockIdx.x) * blockDim.x + threadIdx.x;
+    if (b >= static_cast<long long>(n_chains) * R) return;
+    const int ch = static_cast<int>(b / R), r = static_cast<int>(b % R);
+    if (r == 0) e.swap_ctr[ch] += 1u;
+    if (istep == 2 && r < R - 1 && ((r ^ i0) & 1)) {
+        double* W = e.work + (static_cast<size_t>(ch) * (R - 1) + r) * 2;
+        W[0] = 0.0;
+        W[1] = 0.0;
+    }
+    const size_t k = static_cast<size_t>(ch) * R + r;
+    const int Tr = e.temp_of_slot[k];
+    int* rs = e.rt_state + k;
+    long long* rtt = reinterpret_cast<long long*>(e.rt_trips) + k;
+    if (Tr == 0) {
+        if (*rs == 2) *rtt += 1;
+        *rs = 1;
+    } else if (Tr == R - 1) {
+        if (*rs == 1) *rs = 2;
+    }
+}
+
+// Even or odd pairs where the launch holds many: one workgroup per (chain, pair), the
+// replica of one leg in LDS at a time.  x is cooled first and its owned sites kept in
+// registers, then y is loaded and heated in the same LDS; the pair is decided at once and
+// written back only if accepted.  The per-leg launch writes both candidates of every pair,
+// decides in a second launch and copies the accepted ones in a third; the legs' arithmetic,
+// order and sums are the same here.  VALU-bound (the site maps).  Binary32 L = 16, 128
+// chains x 59 temperatures: 232 us a call, against 343 in three launches; binary64 x 24:
+// 574 against 1078 (its 96 KB of LDS leave one workgroup per CU, here of 512 threads,
+// there of 256).  1024 threads in binary32 from 1024 sites of a sublattice: two workgroups
+// per CU at full occupancy, 61 registers.
+template <typename T, int L, int NT>
+__global__ void __launch_bounds__(NT, sizeof(T) == 4 && NT == 1024 ? 8 : 1) k_coolheat_pair(hsg_ensemble e, ChEps ce, int i0, int npc) {
+    constexpr int N = L * L * L, NH = N / 2, K = (NH + NT - 1) / NT;
+    constexpr int NV = 3 * N * static_cast<int>(sizeof(T)) / 16;
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    T* sh = reinterpret_cast<T*>(smem_raw);
+    __shared__ double red[NT / 64];
+    __shared__ int s_ok;
+    const int t = static_cast<int>(threadIdx.x), R = e.n_temps;
+    const int b = xcd_order(static_cast<int>(blockIdx.x), static_cast<int>(gridDim.x));
+    const int ch = b / npc, i = i0 + 2 * (b % npc);
+    const int x = label(e.slot_of_temp[static_cast<size_t>(ch) * R + i], R, e.guard);
+    const int y = label(e.slot_of_temp[static_cast<size_t>(ch) * R + i + 1], R, e.guard);
+    const T eps = ch_eps<T>(ce, i);
+    const T* __restrict__ J = static_cast<const T*>(e.couplings) + static_cast<size_t>(ch / e.n_chains) * 3 * N;
+    T* spins = static_cast<T*>(e.spins);
+    T* gx = spins + (static_cast<size_t>(ch) * R + x) * 3 * N;
+    T* gy = spins + (static_cast<size_t>(ch) * R + y) * 3 * N;
+    uint4* s4 = reinterpret_cast<uint4*>(sh);
+    T xs[2][K][3];  // C x: the thread's sites
+    double LD[2], H[2];
+    const auto leg = [&](auto heat_c, const T* g) __attribute__((always_inline)) {
+        constexpr bool HEAT = decltype(heat_c)::value;
+        for (int v = t; v < NV; v += NT) s4[v] = reinterpret_cast<const uint4*>(g)[v];
+        __syncthreads();
+        double ld = 0.0, en = 0.0;
+#pragma unroll
+        for (int step = 0; step < 2; ++step) {
+            const int p = HEAT ? 1 - step : step;
+            const T* o = sh + (1 - p) * NH;
+            T* w = sh + p * NH;
+            // an opaque copy, or the neighbours and couplings of the four half-steps are
+            // found once and held in registers
+            int tt = t;
+            asm volatile("" : "+v"(tt));
+#pragma unroll  // the sites of a thread are independent: their latency chains interleave
+            for (int k = 0; k < K; ++k) {
+                const int h = tt + k * NT;
+                if (NH % NT != 0 && h >= NH) break;
+                const Nbr nb = neighbours<L>(h, p, L);
+                T Sx = T(0), Sy = T(0), Sz = T(0);
+#pragma unroll
+                for (int d = 0; d < 6; ++d) {
+                    const int mu = d >> 1;
+                    const T jj = (d & 1) ? J[(mu * 2 + (1 - p)) * NH + nb.n[d]] : J[(mu * 2 + p) * NH + h];
+                    Sx = fma(jj, o[nb.n[d]], Sx);
+                    Sy = fma(jj, o[2 * NH + nb.n[d]], Sy);
+                    Sz = fma(jj, o[4 * NH + nb.n[d]], Sz);
+                }
+                T sx = w[h], sy = w[2 * NH + h], sz = w[4 * NH + h];
+                ld += coolheat_site<T, HEAT>(sx, sy, sz, Sx, Sy, Sz, eps);
+                w[h] = sx;
+                w[2 * NH + h] = sy;
+                w[4 * NH + h] = sz;
+                if constexpr (!HEAT) {
+                    xs[p][k][0] = sx;
+                    xs[p][k][1] = sy;
+                    xs[p][k][2] = sz;
+                }
+                if (step == 1) {
+                    const double dx = sx, dy = sy, dz = sz;
+                    en += fma(dz, static_cast<double>(Sz), fma(dy, static_cast<double>(Sy), dx * static_cast<double>(Sx)));
+                }
+            }
+            __syncthreads();
+        }
+        LD[HEAT ? 1 : 0] = block_sum<NT>(ld, red);
+        H[HEAT ? 1 : 0] = -block_sum<NT>(en, red);
+    };
+    leg(std::false_type{}, gx);
+    leg(std::true_type{}, gy);
+    if (t == 0) {
+        double* W = e.work + (static_cast<size_t>(ch) * (R - 1) + i) * 2;
+        double* en = e.energy + static_cast<size_t>(ch) * R;
+        long long* st = reinterpret_cast<long long*>(e.swap_stats) + (static_cast<size_t>(ch) * (R - 1) + i) * 2;
+        W[0] = LD[0];
+        W[1] = LD[1];
+        if (isnan(LD[0]) || isnan(LD[1])) atomicOr(e.guard, 8);
+        const double b1 = e.betas[i], b2 = e.betas[i + 1];
+        const double lnA = b1 * en[x] + b2 * en[y] - b1 * H[1] - b2 * H[0] + LD[0] - LD[1];
+        const Words w = philox(static_cast<uint32_t>(i), e.swap_ctr[ch], e.chain_base + static_cast<uint32_t>(ch),
+                               kTagSwap << 24, key_lo(e.seed), key_hi(e.seed));
+        st[0] += 1;
+        const bool ok = log(u01_52(w.w0, w.w1)) < lnA;
+        if (ok) {
+            int* sot = e.slot_of_temp + static_cast<size_t>(ch) * R;
+            int* tos = e.temp_of_slot + static_cast<size_t>(ch) * R;
+            en[x] = H[0];
+            en[y] = H[1];
+            sot[i] = y;
+            sot[i + 1] = x;
+            tos[x] = i + 1;
+            tos[y] = i;
+            st[1] += 1;
+        }
+        s_ok = ok ? 1 : 0;
+    }
+    __syncthreads();
+    if (!s_ok) return;
+#pragma unroll
+    for (int p = 0; p < 2; ++p)
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const int h = t + k * NT;
+            if (NH % NT != 0 && h >= NH) break;
+#pragma unroll
+            for (int mu = 0; mu < 3; ++mu) gx[(mu * 2 + p) * NH + h] = xs[p][k][mu];
+        }
+    for (int v = t; v < NV; v += NT) reinterpret_cast<uint4*>(gy)[v] = s4[v];
 }
 
 // Ascending binary32 pass, second launch (the first heats the configuration at
@@ -796,16 +940,9 @@ static hipError_t go_leg_res(const hsg_ensemble& e, const ChEps& ce, int i0, int
     constexpr int NTMAX = sizeof(T) == 4 ? 1024 : 512;
     constexpr int NT1 = NH >= NTMAX ? NTMAX : ((NH + 63) / 64) * 64;
     constexpr int NTS = NT1 > kChThreads ? NT1 : kChThreads;
-    if (npc == 1) {
-        if (prev) return go_leg_nt<T, L, NTS, true>(e, ce, i0, istep, npc, blocks, st);
-        return go_leg_nt<T, L, NTS, false>(e, ce, i0, istep, npc, blocks, st);
-    }
-    if (prev) return hipErrorInvalidValue;
-    // many pairs per launch: binary32 legs with 512 threads, so that the three
-    // workgroups one CU's LDS holds at L = 16 carry 24 waves rather than 12 (measured
-    // 14 % faster at L = 16; binary64 legs, at 151 registers, lose occupancy instead)
-    constexpr int NTM = (sizeof(T) == 4 && NH >= 512) ? 512 : kChThreads;
-    return go_leg_nt<T, L, NTM, false>(e, ce, i0, istep, npc, blocks, st);
+    if (npc != 1) return hipErrorInvalidValue;  // (k_coolheat_pair)
+    if (prev) return go_leg_nt<T, L, NTS, true>(e, ce, i0, istep, npc, blocks, st);
+    return go_leg_nt<T, L, NTS, false>(e, ce, i0, istep, npc, blocks, st);
 }
 
 // Legs of the pairs i0 + istep m; prev (ascending, one pair per chain, L <= 16): the
@@ -853,10 +990,41 @@ static hipError_t launch_decide_copy(const hsg_ensemble& e, int i, int istep, in
     return hipGetLastError();
 }
 
+template <typename T, int L>
+static hipError_t go_pair(const hsg_ensemble& e, const ChEps& ce, int i0, int npc, hipStream_t st) {
+    constexpr int NH = L * L * L / 2, NT = NH >= 1024 && sizeof(T) == 4 ? 1024 : NH >= 512 ? 512 : kChThreads;
+    constexpr size_t lds = 3 * L * L * L * sizeof(T);
+    auto kern = k_coolheat_pair<T, L, NT>;
+    const hipError_t err = allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds);
+    if (err != hipSuccess) return err;
+    hipLaunchKernelGGL(kern, dim3(e.n_samples * e.n_chains * npc), dim3(NT), lds, st, e, ce, i0, npc);
+    const long long n_fin = static_cast<long long>(e.n_samples) * e.n_chains * e.n_temps;
+    hipLaunchKernelGGL(k_coolheat_finish, dim3(static_cast<unsigned>((n_fin + 255) / 256)), dim3(256), 0, st, e, i0, 2);
+    return hipGetLastError();
+}
+
+template <typename T>
+static hipError_t go_pairs(const hsg_ensemble& e, const ChEps& ce, int i0, int npc, hipStream_t st) {
+    switch (e.L) {
+        case 4: return go_pair<T, 4>(e, ce, i0, npc, st);
+        case 6: return go_pair<T, 6>(e, ce, i0, npc, st);
+        case 8: return go_pair<T, 8>(e, ce, i0, npc, st);
+        case 10: return go_pair<T, 10>(e, ce, i0, npc, st);
+        case 12: return go_pair<T, 12>(e, ce, i0, npc, st);
+        case 14: return go_pair<T, 14>(e, ce, i0, npc, st);
+        default: return go_pair<T, 16>(e, ce, i0, npc, st);
+    }
+}
+
 static hipError_t coolheat_round(const hsg_ensemble& e, const ChEps& ce, int i0, int istep, int npc, int last,
                                  hipStream_t st) {
     const int n_chains = e.n_samples * e.n_chains;
     hipError_t err = hipSuccess;
+    // even or odd pairs at L <= 16: both legs in one workgroup, but for a single pair per
+    // chain, whose legs are sooner done side by side (binary32 L = 16, 16 chains x 3
+    // temperatures: 18.4 against 21.4 us; binary64 90 against 107)
+    if (e.L <= 16 && npc > 1)
+        return e.precision == HSG_FP64 ? go_pairs<double>(e, ce, i0, npc, st) : go_pairs<float>(e, ce, i0, npc, st);
     if (npc > 0) {
         err = e.precision == HSG_FP64 ? go_legs<double>(e, ce, i0, istep, npc, false, st)
                                       : go_legs<float>(e, ce, i0, istep, npc, false, st);
@@ -864,7 +1032,8 @@ static hipError_t coolheat_round(const hsg_ensemble& e, const ChEps& ce, int i0,
     }
     if (npc == 1) return launch_decide_copy(e, i0, istep, last, st);  // decision and copy-back in one launch
     if (npc == 0) {  // no pair selected (R = 2, odd pairs): the counters alone
-        hipLaunchKernelGGL(k_coolheat_finish, dim3((n_chains + 63) / 64), dim3(64), 0, st, e, i0, istep);
+        const long long n_fin = static_cast<long long>(n_chains) * e.n_temps;
+        hipLaunchKernelGGL(k_coolheat_finish, dim3(static_cast<unsigned>((n_fin + 255) / 256)), dim3(256), 0, st, e, i0, istep);
         return hipGetLastError();
     }
     (void)last;  // even / odd pairs: one call is one round
@@ -889,7 +1058,7 @@ static hipError_t coolheat_round(const hsg_ensemble& e, const ChEps& ce, int i0,
 // reads it in the slot's spins or in the slot's candidate and writes the other of the two,
 // which an accepted pair makes the configuration; so no launch copies, and k_ch_settle
 // decides the last pair and copies, once per slot, what ended in a candidate.
-// k_ch_split_finish advances the exchange counter and the round trips.
+// k_coolheat_finish advances the exchange counter and the round trips.
 //
 // What bounds it: the chain of launches, two per pair, each a round trip to memory for
 // the sums, one for the configuration and the site map, on 256 CUs with one or two sites
@@ -1220,28 +1389,6 @@ __global__ void __launch_bounds__(kChThreads) k_ch_settle(hsg_ensemble e, ChGrou
     for (int k = part * kChSettle + static_cast<int>(threadIdx.x); k < end; k += kChThreads) dst[k] = src[k];
 }
 
-// Per chain, after the pass: exchange counter and round trips.
-__global__ void k_ch_split_finish(hsg_ensemble e) {
-    // one thread per (chain, slot): slot r's round-trip state from its temperature; the
-    // thread of slot 0 advances the chain's counter
-    const int n_chains = e.n_samples * e.n_chains;
-    const int R = e.n_temps;
-    const long long b = static_cast<long long>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (b >= static_cast<long long>(n_chains) * R) return;
-    const int ch = static_cast<int>(b / R), r = static_cast<int>(b % R);
-    if (r == 0) e.swap_ctr[ch] += 1u;
-    const size_t k = static_cast<size_t>(ch) * R + r;
-    const int Tr = e.temp_of_slot[k];
-    int* rs = e.rt_state + k;
-    long long* rtt = reinterpret_cast<long long*>(e.rt_trips) + k;
-    if (Tr == 0) {
-        if (*rs == 2) *rtt += 1;
-        *rs = 1;
-    } else if (Tr == R - 1) {
-        if (*rs == 1) *rs = 2;
-    }
-}
-
 // Workgroups per leg for the split pass (L > 16): cooling about 512 per launch, a site per
 // thread at least; heating up to eight of 2048 sites; both within the scratch's partial
 // area.  G = 1: not split.
@@ -1279,7 +1426,7 @@ static hipError_t coolheat_split_pass(const hsg_ensemble& e, const ChEps& ce, Ch
     const int parts = (3 * e.L * e.L * e.L + kChSettle - 1) / kChSettle;
     hipLaunchKernelGGL(k_ch_settle<T>, dim3(static_cast<unsigned>(chains) * R * parts), nt, 0, st, e, gr, parts);
     const long long n_fin = static_cast<long long>(chains) * R;
-    hipLaunchKernelGGL(k_ch_split_finish, dim3(static_cast<unsigned>((n_fin + 255) / 256)), dim3(256), 0, st, e);
+    hipLaunchKernelGGL(k_coolheat_finish, dim3(static_cast<unsigned>((n_fin + 255) / 256)), dim3(256), 0, st, e, 0, 1);
     return hipGetLastError();
 }
 
