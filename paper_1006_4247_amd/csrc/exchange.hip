@@ -384,19 +384,27 @@ __global__ void k_anneal_copyback(hsg_ensemble e) {
 
 // ---------------------------------------------------------------- measurement
 // Q_ab = sum_x s^(0)_{a,x} s^(1)_{b,x} between chains 0 and 1 at temperature b,
-// chi = Q:Q / N (paper Sec. II); e = H/N by temperature.  Workgroup per (sample, b).
+// chi = Q:Q / N (paper Sec. II); e = H/N by temperature.  Workgroup per (sample, b), or per
+// slice of one (`slices` of them, see measure_slices), which leaves its nine sums in the
+// scratch's candidate area for k_measure_sum.
 // FIN: first finish a streaming sweep whose last finishing pass was left out: the
 // energy of each slot it reads from the per-tile sums (n_tiles of them, added in tile
 // order, as k_stream_finalize adds them), and sweep_ctr += ctr_add.  Every slot is one
 // (sample, chain, temperature), so each is finished by exactly one workgroup.
+__device__ __forceinline__ double* measure_sums(const hsg_ensemble& e) {
+    return reinterpret_cast<double*>(static_cast<unsigned char*>(e.scratch) + scratch_layout(e).cand);
+}
+
 template <typename T, int NT, bool FIN = false>
-__global__ void __launch_bounds__(NT) k_measure(hsg_ensemble e, int n_tiles = 0, int ctr_add = 0) {
+__global__ void __launch_bounds__(NT) k_measure(hsg_ensemble e, int n_tiles, int ctr_add, int slices) {
     constexpr int NW = NT / 64;
     __shared__ double red[9 * NW];
     const int N = e.L * e.L * e.L;
     const int R = e.n_temps, C = e.n_chains;
-    const int smp = blockIdx.x / R, b = blockIdx.x % R;
-    if (FIN) {
+    const int slice = blockIdx.x % slices, sb = blockIdx.x / slices;
+    const int smp = sb / R, b = sb % R;
+    if (slice != 0) {  // (the first slice's workgroup takes the energies)
+    } else if (FIN) {
         // one wave per chain: its lanes load 64 per-tile sums at a time, which are then
         // added one lane after another (the finishing pass's order)
         const ScratchLayout sl = scratch_layout(e);
@@ -436,7 +444,8 @@ __global__ void __launch_bounds__(NT) k_measure(hsg_ensemble e, int n_tiles = 0,
     const Vec* c = reinterpret_cast<const Vec*>(static_cast<const T*>(e.spins) + static_cast<size_t>(s2) * 3 * N);
     double q[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll 4  // all loads of a 16^3 replica pair issued before the first use
-    for (int v = threadIdx.x; v < NV; v += NT) {
+    for (int v = static_cast<int>(static_cast<long long>(NV) * slice / slices) + static_cast<int>(threadIdx.x);
+         v < static_cast<int>(static_cast<long long>(NV) * (slice + 1) / slices); v += NT) {
         const Vec a0 = a[v], a1 = a[NV + v], a2 = a[2 * NV + v];
         const Vec c0 = c[v], c1 = c[NV + v], c2 = c[2 * NV + v];
 #pragma unroll
@@ -460,11 +469,33 @@ __global__ void __launch_bounds__(NT) k_measure(hsg_ensemble e, int n_tiles = 0,
         for (int k = 0; k < 9; ++k) {
             double t = 0.0;
             for (int w = 0; w < NW; ++w) t += red[k * NW + w];
+            if (slices > 1) {
+                measure_sums(e)[static_cast<size_t>(blockIdx.x) * 9 + k] = t;
+                continue;
+            }
             e.Q[(static_cast<size_t>(smp) * R + b) * 9 + k] = t;
             chi += t * t;
         }
-        e.chi[static_cast<size_t>(smp) * R + b] = chi / static_cast<double>(N);
+        if (slices == 1) e.chi[static_cast<size_t>(smp) * R + b] = chi / static_cast<double>(N);
     }
+}
+
+// Q and chi of one (sample, temperature) per wave from its slices' sums, in order.
+__global__ void __launch_bounds__(64) k_measure_sum(hsg_ensemble e, int slices) {
+    const int k = static_cast<int>(threadIdx.x);
+    double t = 0.0;
+    if (k < 9) {
+        const double* sums = measure_sums(e) + static_cast<size_t>(blockIdx.x) * slices * 9 + k;
+#pragma unroll 16  // (loads in flight)
+        for (int g = 0; g < slices; ++g) t += sums[g * 9];
+        e.Q[static_cast<size_t>(blockIdx.x) * 9 + k] = t;
+    }
+    double chi = 0.0;
+    for (int j = 0; j < 9; ++j) {
+        const double q = readlane_f64(t, j);
+        chi += q * q;
+    }
+    if (k == 0) e.chi[blockIdx.x] = chi / (static_cast<double>(e.L) * e.L * e.L);
 }
 
 // ---------------------------------------------------------------- launchers
@@ -528,40 +559,43 @@ hipError_t launch_anneal_decide(const hsg_ensemble& e, int parity, hipStream_t s
 // size depends on L alone, so a sample range measured on its own sums in the same order.
 constexpr int kMeasureThreadsLarge = 512;
 
-hipError_t launch_measure(const hsg_ensemble& e, hipStream_t st) {
-    const int blocks = e.n_samples * e.n_temps;
+// Slices of a pair of replicas beyond L = 32, by L alone (as above), where the scratch is
+// given: a workgroup reads the pair at the 60 GB/s one CU takes in, so the few workgroups
+// there are leave the memory idle (L = 64, 2 x 9 of them, 113 MB: 107 us, in 32 slices 26 + 5).  At L <= 32 a
+// second launch costs about what slices save.
+static int measure_slices(const hsg_ensemble& e) {
+    const int N = e.L * e.L * e.L;
+    const bool scratch = e.scratch && reinterpret_cast<uintptr_t>(e.scratch) % 256 == 0;
+    return e.L > 32 && scratch && e.n_chains >= 2 && e.Q ? N / 8192 : 1;
+}
+
+template <bool FIN>
+static hipError_t go_measure(const hsg_ensemble& e, int n_tiles, int ctr_add, hipStream_t st) {
+    const int pairs = e.n_samples * e.n_temps;
     if (e.L > 16) {
         constexpr int NT = kMeasureThreadsLarge;
+        const int slices = measure_slices(e);
+        const dim3 blocks(static_cast<unsigned>(pairs) * slices);
         if (e.precision == HSG_FP64)
-            hipLaunchKernelGGL((k_measure<double, NT>), dim3(blocks), dim3(NT), 0, st, e, 0, 0);
+            hipLaunchKernelGGL((k_measure<double, NT, FIN>), blocks, dim3(NT), 0, st, e, n_tiles, ctr_add, slices);
         else
-            hipLaunchKernelGGL((k_measure<float, NT>), dim3(blocks), dim3(NT), 0, st, e, 0, 0);
+            hipLaunchKernelGGL((k_measure<float, NT, FIN>), blocks, dim3(NT), 0, st, e, n_tiles, ctr_add, slices);
+        if (slices > 1) hipLaunchKernelGGL(k_measure_sum, dim3(pairs), dim3(64), 0, st, e, slices);
         return hipGetLastError();
     }
     // one (sample, temperature) per 128-thread workgroup: 1536 of them at L = 16, 64 x 24
     // (measured 26.4 us per pass against 27.3 with 256 threads and 28.1 with 512)
     if (e.precision == HSG_FP64)
-        hipLaunchKernelGGL((k_measure<double, 128>), dim3(blocks), dim3(128), 0, st, e, 0, 0);
+        hipLaunchKernelGGL((k_measure<double, 128, FIN>), dim3(pairs), dim3(128), 0, st, e, n_tiles, ctr_add, 1);
     else
-        hipLaunchKernelGGL((k_measure<float, 128>), dim3(blocks), dim3(128), 0, st, e, 0, 0);
+        hipLaunchKernelGGL((k_measure<float, 128, FIN>), dim3(pairs), dim3(128), 0, st, e, n_tiles, ctr_add, 1);
     return hipGetLastError();
 }
 
+hipError_t launch_measure(const hsg_ensemble& e, hipStream_t st) { return go_measure<false>(e, 0, 0, st); }
+
 hipError_t launch_measure_fin(const hsg_ensemble& e, int n_tiles, int ctr_add, hipStream_t st) {
-    const int blocks = e.n_samples * e.n_temps;
-    if (e.L > 16) {
-        constexpr int NT = kMeasureThreadsLarge;
-        if (e.precision == HSG_FP64)
-            hipLaunchKernelGGL((k_measure<double, NT, true>), dim3(blocks), dim3(NT), 0, st, e, n_tiles, ctr_add);
-        else
-            hipLaunchKernelGGL((k_measure<float, NT, true>), dim3(blocks), dim3(NT), 0, st, e, n_tiles, ctr_add);
-    } else {
-        if (e.precision == HSG_FP64)
-            hipLaunchKernelGGL((k_measure<double, 128, true>), dim3(blocks), dim3(128), 0, st, e, n_tiles, ctr_add);
-        else
-            hipLaunchKernelGGL((k_measure<float, 128, true>), dim3(blocks), dim3(128), 0, st, e, n_tiles, ctr_add);
-    }
-    return hipGetLastError();
+    return go_measure<true>(e, n_tiles, ctr_add, st);
 }
 
 }  // namespace hsg
