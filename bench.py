@@ -633,8 +633,9 @@ def uneven_study(torch, hsg, steps, warm=20):
     """Steps of the uneven batch (sweep 1 HB + 3 OR, measurement, plain exchange of all
     pairs ascending, per class) replayed from the library's captured cycle: site updates
     per ns over the batch, and the algorithmic HBM bytes of its sweeps per second
-    (LDS-resident classes: the parity-1 half of every replica read and all of it written
-    once per sweep, couplings once; streaming classes, one launch per half-sweep: per
+    (LDS- and register-resident classes, the default at every size of the batch: the
+    parity-1 half of every replica read and all of it written once per sweep, couplings
+    once; streaming, one launch per half-sweep: per
     half-sweep the updated half read and written and the other half read, couplings once
     per sample; wavefront: one read and one write per lattice sweep).  Four forms: the
     library's default kernels with the classes one after another, the same with each
@@ -650,8 +651,8 @@ def uneven_study(torch, hsg, steps, warm=20):
         e.init_spins()
     out = {"study": "uneven-batch", "chains": 2, "steps": steps,
            "data": "synthetic (Gaussian J_xy and random unit spins from Philox, seed %#x)" % UNEVEN["seed"]}
-    # the streaming classes (HBM-bound) one after another on one stream, so that each has
-    # the MALL to itself, and the LDS-resident classes (compute-bound) beside them on another
+    # the classes above L = 16 one after another on one stream, the LDS-resident ones beside
+    # them on another
     grouped = [1 if e.L <= 16 else 0 for e in ens]
     for key, tun, conc in (("default_kernels_in_sequence", None, False), ("default_kernels_concurrent", None, True),
                            ("streaming_beside_resident", None, grouped), ("autotuned", "auto", "auto")):
@@ -671,7 +672,8 @@ def uneven_study(torch, hsg, steps, warm=20):
         classes = []
         for e, t in zip(ens, run.tunings):
             N, slots = e.N, e.n_slots
-            path = (t or {}).get("path", 0) or (3 if e.L <= 16 else 2)
+            # (by default the classes above L = 16 are register-resident here)
+            path = (t or {}).get("path", 0) or 3
             if path in (1, 3, 6):  # one launch per sweep
                 b = slots * (3 * (N // 2) * 4 + 3 * N * 4) + e.S * 3 * N * 4
             elif path == 4:  # one pass per lattice sweep: read all, write all
@@ -847,6 +849,8 @@ def headline(torch, hsg, w, steps, warmup, clock_warmup_s, fused_ok=True, split=
     # the dominant kernel (the step's sweep, with the measurement where the library
     # fuses it): back-to-back launches on this stream, events around them
     name, fused = step_kernel(w, fused_ok)
+    if w["prec"] == "fp64" and w["L"] == 16:
+        name = "k_column<double,16>"  # (the register-resident kernel takes these sweeps)
 
     def launch():
         if fused:
