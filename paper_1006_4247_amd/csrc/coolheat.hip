@@ -1012,7 +1012,8 @@ static hipError_t go_pairs(const hsg_ensemble& e, const ChEps& ce, int i0, int n
         case 10: return go_pair<T, 10>(e, ce, i0, npc, st);
         case 12: return go_pair<T, 12>(e, ce, i0, npc, st);
         case 14: return go_pair<T, 14>(e, ce, i0, npc, st);
-        default: return go_pair<T, 16>(e, ce, i0, npc, st);
+        case 16: return go_pair<T, 16>(e, ce, i0, npc, st);
+        default: return hipErrorInvalidValue;  // (L = 2 and L > 16: the generic legs)
     }
 }
 
@@ -1020,10 +1021,10 @@ static hipError_t coolheat_round(const hsg_ensemble& e, const ChEps& ce, int i0,
                                  hipStream_t st) {
     const int n_chains = e.n_samples * e.n_chains;
     hipError_t err = hipSuccess;
-    // even or odd pairs at L <= 16: both legs in one workgroup, but for a single pair per
+    // even or odd pairs at L = 4 .. 16: both legs in one workgroup, but for a single pair per
     // chain, whose legs are sooner done side by side (binary32 L = 16, 16 chains x 3
     // temperatures: 18.4 against 21.4 us; binary64 90 against 107)
-    if (e.L <= 16 && npc > 1)
+    if (e.L >= 4 && e.L <= 16 && npc > 1)
         return e.precision == HSG_FP64 ? go_pairs<double>(e, ce, i0, npc, st) : go_pairs<float>(e, ce, i0, npc, st);
     if (npc > 0) {
         err = e.precision == HSG_FP64 ? go_legs<double>(e, ce, i0, istep, npc, false, st)
