@@ -29,7 +29,9 @@
 // that replicas beyond a multiple of 256 wait for a round of their own.
 //
 // Spins are those of the other sweep kernels bit for bit (same site arithmetic, order of
-// the field's terms and random numbers).
+// the field's terms and random numbers), and so are the energies of sweeps where the size of
+// an ensemble or the length of a call decides between this kernel and the streaming ones
+// (column_energy).
 #include "hsg_device.h"
 #include "hsg_launch.h"
 
@@ -78,10 +80,19 @@ struct Column : ColumnShape<T, L> {
     static constexpr bool JZ = BZ == 0;  // bonds along z in registers
     static constexpr int JN = JZ ? 4 : 6;
     static constexpr int HZ = ColumnShape<T, L>::HZ;  // planes of each half of the lattice per heat-bath step (BZ > 0)
+    // the energy's site terms (see column_energy): their words over the site's uniforms, or
+    // over the sublattice once it has been read, or (pairs of sites) beyond the batches
+    static constexpr size_t TERMS = BZ      ? 6 * BZ * static_cast<size_t>(PL) * sizeof(T)
+                                    : DRAWN ? 3 * static_cast<size_t>(NH) * sizeof(T)
+                                            : 0;
+    static constexpr size_t WAVES = DRAWN ? 0 : TERMS + (BZ ? NQ : NH) * 8;  // (the sublattice has been read)
+    static constexpr int NG = (NQ + 63) / 64;  // waves of site pairs
+    static constexpr bool TILED = !(sizeof(T) == 8 && L == 16);  // energies in the streaming kernels' order
     static constexpr size_t LDS = (BZ ? (12 * HZ + 12 > 6 * BZ ? 12 * HZ + 12 : 6 * BZ) * static_cast<size_t>(PL)
                                       : (DRAWN ? 5 : 3) * static_cast<size_t>(NH)) *
                                   sizeof(T);
     static_assert(L % ZP == 0 && ZP >= 2 && NT <= 1024, "one workgroup");
+    static_assert(TERMS % 8 == 0 && WAVES % 8 == 0 && WAVES + NG * 8 <= LDS && NG <= 256, "room for the terms");
     static_assert(BZ == 0 || (ZG == 1 && L % BZ == 0 && NB % 2 == 0), "whole columns, batches in turn in two buffers");
 };
 
@@ -157,8 +168,10 @@ __device__ __forceinline__ void column_publish(const ColumnState<T, L>& c, T* __
 }
 
 // One half-sweep of sublattice P: KIND 1 heat-bath, 2 overrelaxation, 3 overrelaxation
-// with the energy, 0 general (kind, renormalisation and energy from the arguments).
-template <typename T, int L, int P, int KIND>
+// with the energy, 0 general (kind, renormalisation and energy from the arguments).  The
+// energy's terms are added up in `acc` (SUM) or left in LDS for column_energy, where nothing
+// reads the sublattice or the uniforms after the call's last half-sweep.
+template <typename T, int L, int P, int KIND, bool SUM>
 __device__ __forceinline__ void column_half(ColumnState<T, L>& c, T* __restrict__ lds, bool hb_arg, bool rn_arg,
                                             bool want_arg, int hs, T beta, uint32_t tsw, double& acc, bool& bad) {
     using M = Column<T, L>;
@@ -174,6 +187,9 @@ __device__ __forceinline__ void column_half(ColumnState<T, L>& c, T* __restrict_
     const auto at = [&](int off, int el) -> T& {  // LDS: byte offset of a thread + constant element
         return *reinterpret_cast<T*>(reinterpret_cast<unsigned char*>(lds) + off + el * M::B);
     };
+    double* const terms = reinterpret_cast<double*>(reinterpret_cast<unsigned char*>(lds) + M::TERMS) + c.own / M::B;
+    constexpr bool HELD = !SUM && BZ == 0 && !M::DRAWN;  // terms in registers until the sublattice has been read
+    double term[HELD ? ZP : 1];
     T* rnd = lds + 3 * NH;
     if (M::DRAWN && hb) {  // one Philox block per site pair (h, h + N/4)
         for (int h = static_cast<int>(threadIdx.x); h < NQ; h += NT) {
@@ -266,10 +282,25 @@ __device__ __forceinline__ void column_half(ColumnState<T, L>& c, T* __restrict_
         c.s[P][m][2] = oz;
         if (want) {
             const double dx = ox, dy = oy, dz = oz;
-            acc += fma(dz, static_cast<double>(S[2]), fma(dy, static_cast<double>(S[1]), dx * static_cast<double>(S[0])));
+            double t = fma(dz, static_cast<double>(S[2]), fma(dy, static_cast<double>(S[1]), dx * static_cast<double>(S[0])));
             const double n2 = fma(dz, dz, fma(dy, dy, dx * dx));
             if (!(fabs(n2 - 1.0) <= NormTol<T>::value)) bad = true;
-            asm volatile("" : "+v"(acc));  // or the sums are put off and every spin and field held for them
+            if constexpr (SUM) {
+                acc += t;
+                asm volatile("" : "+v"(acc));  // or the sums are put off and every spin and field held for them
+            } else if constexpr (BZ > 0) {  // planes m and m + L/2 are the thread's own
+                if constexpr (m < ZP / 2)
+                    terms[m * PL] = t;
+                else
+                    terms[(m - ZP / 2) * PL] += t;
+            } else if constexpr (M::DRAWN) {
+                const long long w = __double_as_longlong(t);
+                at(c.own, 3 * NH + m * PL) = __int_as_float(static_cast<int>(w));
+                at(c.own, 4 * NH + m * PL) = __int_as_float(static_cast<int>(w >> 32));
+            } else {
+                asm volatile("" : "+v"(t));  // (as above)
+                term[m] = t;
+            }
         }
         if ((M::FENCE & 2) || ((M::FENCE & 4) && (m & 1))) __builtin_amdgcn_sched_barrier(0);
         if (BZ > 0 && m % (BZ > 0 ? BZ : 1) == BZ - 1 && m + 1 < ZP) lds_barrier();
@@ -279,7 +310,10 @@ __device__ __forceinline__ void column_half(ColumnState<T, L>& c, T* __restrict_
     column_bonds<T, L, Q>(c, c.jb[1], 1, so);
     lds_barrier();  // every thread has read the other sublattice
     if constexpr (BZ == 0) {
-        if ((M::FENCE & 8) == 0 || c.on) {
+        if (HELD && want) {
+#pragma unroll
+            for (int m = 0; m < ZP; ++m) terms[m * PL] = term[HELD ? m : 0];
+        } else if ((M::FENCE & 8) == 0 || c.on) {
 #pragma unroll
             for (int m = 0; m < ZP; ++m)
 #pragma unroll
@@ -287,6 +321,49 @@ __device__ __forceinline__ void column_half(ColumnState<T, L>& c, T* __restrict_
         }
         lds_barrier();
     }
+}
+
+// The energy of the replica from the terms the call's last half-sweep left in LDS, in the
+// order in which the streaming kernels add them (sites h and h + N/4, the wave butterfly,
+// four waves of a 256-thread tile, the tiles): an ensemble's energies are then the same bits
+// whichever of the two kernels takes a call, so that neither the size of an ensemble (a
+// shard of it, say) nor the length of a call can change an exchange decision.  Every thread
+// receives the result.
+template <typename T, int L>
+__device__ __forceinline__ double column_energy(T* __restrict__ lds, double& s_H) {
+    using M = Column<T, L>;
+    constexpr int NQ = M::NQ, NG = M::NG, NW = M::NT / 64, TILES = (NG + 3) / 4;
+    static_assert(TILES <= 64, "a lane per tile");
+    unsigned char* const raw = reinterpret_cast<unsigned char*>(lds);
+    double* const waves = reinterpret_cast<double*>(raw + M::WAVES);
+    const auto term = [&](int k) -> double {
+        if constexpr (M::DRAWN) {
+            const int* w = reinterpret_cast<const int*>(raw + M::TERMS);
+            return __hiloint2double(w[M::NH + k], w[k]);
+        }
+        return reinterpret_cast<const double*>(raw + M::TERMS)[k];
+    };
+    const int lane = static_cast<int>(threadIdx.x) & 63, wave = static_cast<int>(threadIdx.x) >> 6;
+#pragma unroll  // (the waves' sums interleave)
+    for (int k = 0; k < (NG + NW - 1) / NW; ++k) {
+        const int g = wave + k * NW, q = g * 64 + lane;
+        double v = 0.0;
+        if (q < NQ) v = M::BZ ? term(q) : term(q) + term(q + NQ);
+        v = wave_sum(v);
+        if (lane == 0 && g < NG) waves[g] = v;
+    }
+    lds_barrier();
+    if (wave == 0) {
+        double tile = 0.0, H = 0.0;
+#pragma unroll
+        for (int w = 0; w < 4; ++w)
+            if (4 * lane + w < NG) tile += waves[4 * lane + w];
+#pragma unroll 4  // (more would spill scalar registers)
+        for (int i = 0; i < TILES; ++i) H -= readlane_f64(tile, i);
+        if (lane == 0) s_H = H;
+    }
+    lds_barrier();
+    return s_H;
 }
 
 // A heat-bath half-sweep of sublattice P where a thread owns whole columns (BZ > 0).  Site
@@ -378,7 +455,7 @@ __device__ __forceinline__ void column_heat(ColumnState<T, L>& c, T* __restrict_
 // One sweep: n_hb heat-bath then n_or overrelaxation lattice sweeps, sublattice 0 before 1,
 // or (ADJ) in reverse.  The loops over kinds are separate so that the spins a thread holds
 // stay in place from one half-sweep to the next.
-template <typename T, int L, bool ADJ>
+template <typename T, int L, bool SUM, bool ADJ>
 __device__ __forceinline__ void column_sweep(ColumnState<T, L>& c, T* __restrict__ lds, int n_hb, int n_or, bool renorm,
                                              bool want, T beta, uint32_t tsw, double& acc, bool& bad) {
     constexpr int P0 = ADJ ? 1 : 0, P1 = 1 - P0;
@@ -390,12 +467,12 @@ __device__ __forceinline__ void column_sweep(ColumnState<T, L>& c, T* __restrict
             column_heat<T, L, 1>(c, lds, 2 * l + 1, beta, tsw);
         }
         for (int l = want ? 1 : 0; l < n_or; ++l) {
-            column_half<T, L, 0, 2>(c, lds, false, false, false, 0, beta, tsw, acc, bad);
-            column_half<T, L, 1, 2>(c, lds, false, false, false, 0, beta, tsw, acc, bad);
+            column_half<T, L, 0, 2, SUM>(c, lds, false, false, false, 0, beta, tsw, acc, bad);
+            column_half<T, L, 1, 2, SUM>(c, lds, false, false, false, 0, beta, tsw, acc, bad);
         }
         if (want) {
-            column_half<T, L, 0, 2>(c, lds, false, false, false, 0, beta, tsw, acc, bad);
-            column_half<T, L, 1, 3>(c, lds, false, false, true, 0, beta, tsw, acc, bad);
+            column_half<T, L, 0, 2, SUM>(c, lds, false, false, false, 0, beta, tsw, acc, bad);
+            column_half<T, L, 1, 3, SUM>(c, lds, false, false, true, 0, beta, tsw, acc, bad);
         }
         return;
     }
@@ -405,20 +482,20 @@ __device__ __forceinline__ void column_sweep(ColumnState<T, L>& c, T* __restrict
     const auto general = [&](int i) {  // i-th lattice sweep of the call's order
         const int l = ADJ ? n_lat - 1 - i : i;
         const bool hb = l < n_hb, rn = renorm && l == n_lat - 1, w = want && i == n_lat - 1;
-        column_half<T, L, P0, 0>(c, lds, hb, rn, false, 2 * l + P0, beta, tsw, acc, bad);
-        column_half<T, L, P1, 0>(c, lds, hb, rn, w, 2 * l + P1, beta, tsw, acc, bad);
+        column_half<T, L, P0, 0, SUM>(c, lds, hb, rn, false, 2 * l + P0, beta, tsw, acc, bad);
+        column_half<T, L, P1, 0, SUM>(c, lds, hb, rn, w, 2 * l + P1, beta, tsw, acc, bad);
     };
     const auto heat = [&](int i0, int i1) {
         for (int i = i0; i < i1; ++i) {
             const int l = ADJ ? n_lat - 1 - i : i;
-            column_half<T, L, P0, 1>(c, lds, true, false, false, 2 * l + P0, beta, tsw, acc, bad);
-            column_half<T, L, P1, 1>(c, lds, true, false, false, 2 * l + P1, beta, tsw, acc, bad);
+            column_half<T, L, P0, 1, SUM>(c, lds, true, false, false, 2 * l + P0, beta, tsw, acc, bad);
+            column_half<T, L, P1, 1, SUM>(c, lds, true, false, false, 2 * l + P1, beta, tsw, acc, bad);
         }
     };
     const auto over = [&](int i0, int i1) {
         for (int i = i0; i < i1; ++i) {
-            column_half<T, L, P0, 2>(c, lds, false, false, false, 0, beta, tsw, acc, bad);
-            column_half<T, L, P1, 2>(c, lds, false, false, false, 0, beta, tsw, acc, bad);
+            column_half<T, L, P0, 2, SUM>(c, lds, false, false, false, 0, beta, tsw, acc, bad);
+            column_half<T, L, P1, 2, SUM>(c, lds, false, false, false, 0, beta, tsw, acc, bad);
         }
     };
     const int end = n_lat - tail;
@@ -426,8 +503,8 @@ __device__ __forceinline__ void column_sweep(ColumnState<T, L>& c, T* __restrict
         heat(0, n_hb < end ? n_hb : end);
         over(n_hb < end ? n_hb : end, end);
         if (tail && n_or > 0 && !renorm) {
-            column_half<T, L, P0, 2>(c, lds, false, false, false, 0, beta, tsw, acc, bad);
-            column_half<T, L, P1, 3>(c, lds, false, false, true, 0, beta, tsw, acc, bad);
+            column_half<T, L, P0, 2, SUM>(c, lds, false, false, false, 0, beta, tsw, acc, bad);
+            column_half<T, L, P1, 3, SUM>(c, lds, false, false, true, 0, beta, tsw, acc, bad);
         } else if (tail) {
             general(end);
         }
@@ -530,6 +607,7 @@ __device__ __forceinline__ double column_run(const hsg_ensemble& e, int slot, co
     const bool renorm = renorm_on(e) && n_hb == 0;
     const int n_iter = LEG ? leg.K + 1 : n_sweeps;
     bool bad = false;
+    constexpr bool SUM = LEG || !M::TILED;
     for (int k = 0; k < n_iter; ++k) {
         double beta_d;
         if (LEG) {
@@ -542,16 +620,15 @@ __device__ __forceinline__ double column_run(const hsg_ensemble& e, int slot, co
         }
         const bool need_e = LEG || k == n_sweeps - 1;
         double acc = 0.0;
-        column_sweep<T, L, ADJ>(c, lds, n_hb, n_or, renorm, need_e, static_cast<T>(beta_d), t0 + static_cast<uint32_t>(k),
+        column_sweep<T, L, SUM, ADJ>(c, lds, n_hb, n_or, renorm, need_e, static_cast<T>(beta_d), t0 + static_cast<uint32_t>(k),
                                 acc, bad);
-        if (need_e) {
+        if (SUM && need_e) {
             const double tot = block_sum<NT, true>(c.on ? acc : 0.0, red);
             if (tid == 0) s_H = -tot;
             lds_barrier();
             H = s_H;
         }
     }
-    if (bad || !isfinite(H)) atomicOr(e.guard, 1);
     if (c.on) {
 #pragma unroll
         for (int p = 0; p < 2; ++p)
@@ -560,6 +637,8 @@ __device__ __forceinline__ double column_run(const hsg_ensemble& e, int slot, co
 #pragma unroll
                 for (int mu = 0; mu < 3; ++mu) gd[(mu * 2 + p) * NH + own + m * PL] = c.s[p][m][mu];
     }
+    if constexpr (!SUM) H = column_energy<T, L>(lds, s_H);  // (the spins need no registers any more)
+    if (bad || !isfinite(H)) atomicOr(e.guard, 1);
     if (tid == 0) e.sweep_ctr[slot] = t0 + static_cast<uint32_t>(LEG ? leg.K : n_sweeps);
     return H;
 }
