@@ -102,8 +102,7 @@ typedef struct hsg_ensemble {
     const double* anneal_lambda;  /* [R-1][anneal_K_max] interior betas, or NULL = linear */
     int32_t anneal_K_max;
     int32_t reserved2;
-    void* scratch;                /* hsg_scratch_bytes() bytes, 256-byte aligned: needed by
-                                     hsg_anneal_swap and by sweeps on the streaming path */
+    void* scratch;                /* hsg_scratch_bytes() bytes, 256-byte aligned, see there */
     double* work;                 /* [S][C][R-1][2] W_up, W_down of the last call */
     /* measurement outputs (may be NULL unless hsg_measure is called) */
     double* Q;      /* [S][R][3][3] */
@@ -147,7 +146,12 @@ int hsg_abi_version(void);
 /* Thread-local message of the last failed call on this thread ("" if none). */
 const char* hsg_last_error(void);
 
-/* Bytes of device scratch one ensemble needs for hsg_anneal_swap. */
+/* Bytes of device scratch of one ensemble.  Needed, and overwritten, by hsg_anneal_swap,
+ * hsg_coolheat_swap[_pairs] and, on the streaming path (by default every lattice beyond one
+ * workgroup's LDS; also hsg_tuning.path 5), hsg_sweep, hsg_sweep_tuned and
+ * hsg_sweep_measure.  hsg_decimate_swap of all pairs at L > 16 overwrites it if it is given.
+ * Nothing is kept there from one call to the next.  The other calls, hsg_measure and
+ * hsg_energy among them, leave it alone. */
 size_t hsg_scratch_bytes(const hsg_ensemble* ens);
 
 /* Draw J_xy ~ N(0,1) for every sample (paper Sec. I: Gaussian couplings of zero
@@ -274,7 +278,8 @@ hsg_status hsg_measure(const hsg_ensemble* ens, int n_ens, void* stream);
  * replicas of a temperature in turn, the couplings loaded once, and then measures
  * them.  On the streaming path the measurement also adds up the last sweep's per-tile energies, in place of
  * the sweep's own finishing launch, in the same order (energies and counters bit for
- * bit those of hsg_sweep).  Other ensembles take the two calls.  Needs what both
+ * bit those of hsg_sweep), and beyond L = 32 reads the two replicas in slices whose sums
+ * stay in the scratch until they are added up.  Other ensembles take the two calls.  Needs what both
  * calls need; n_sweeps = 0 measures only. */
 hsg_status hsg_sweep_measure(const hsg_ensemble* ens, int n_ens, int n_sweeps, int n_hb, int n_or,
                              void* stream);

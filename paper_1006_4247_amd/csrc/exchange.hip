@@ -385,14 +385,16 @@ __global__ void k_anneal_copyback(hsg_ensemble e) {
 // ---------------------------------------------------------------- measurement
 // Q_ab = sum_x s^(0)_{a,x} s^(1)_{b,x} between chains 0 and 1 at temperature b,
 // chi = Q:Q / N (paper Sec. II); e = H/N by temperature.  Workgroup per (sample, b), or per
-// slice of one (`slices` of them, see measure_slices), which leaves its nine sums in the
-// scratch's candidate area for k_measure_sum.
+// slice of one (SLICED, `slices` of them, see measure_slices), which leaves its nine sums in
+// the scratch for k_measure_sum, behind the per-tile sums of the sweep it finishes.
 // FIN: first finish a streaming sweep whose last finishing pass was left out: the
 // energy of each slot it reads from the per-tile sums (n_tiles of them, added in tile
 // order, as k_stream_finalize adds them), and sweep_ctr += ctr_add.  Every slot is one
 // (sample, chain, temperature), so each is finished by exactly one workgroup.
-__device__ __forceinline__ double* measure_sums(const hsg_ensemble& e) {
-    return reinterpret_cast<double*>(static_cast<unsigned char*>(e.scratch) + scratch_layout(e).cand);
+__device__ __forceinline__ double* measure_sums(const hsg_ensemble& e, int smp, int b, int n_tiles) {
+    const ScratchLayout sl = scratch_layout(e);
+    return reinterpret_cast<double*>(static_cast<unsigned char*>(e.scratch) + sl.partial) +
+           (static_cast<size_t>(smp) * e.n_chains * e.n_temps + b) * sl.max_tiles + n_tiles;
 }
 
 template <typename T, int NT, bool FIN, bool SLICED>
@@ -470,23 +472,24 @@ __global__ void __launch_bounds__(NT) k_measure(hsg_ensemble e, int n_tiles, int
         for (int k = 0; k < 9; ++k) {
             double t = 0.0;
             for (int w = 0; w < NW; ++w) t += red[k * NW + w];
-            if (slices > 1) {
-                measure_sums(e)[static_cast<size_t>(blockIdx.x) * 9 + k] = t;
+            if (SLICED) {
+                measure_sums(e, smp, b, n_tiles)[slice * 9 + k] = t;
                 continue;
             }
             e.Q[(static_cast<size_t>(smp) * R + b) * 9 + k] = t;
             chi += t * t;
         }
-        if (slices == 1) e.chi[static_cast<size_t>(smp) * R + b] = chi / static_cast<double>(N);
+        if (!SLICED) e.chi[static_cast<size_t>(smp) * R + b] = chi / static_cast<double>(N);
     }
 }
 
 // Q and chi of one (sample, temperature) per wave from its slices' sums, in order.
-__global__ void __launch_bounds__(64) k_measure_sum(hsg_ensemble e, int slices) {
+__global__ void __launch_bounds__(64) k_measure_sum(hsg_ensemble e, int n_tiles, int slices) {
     const int k = static_cast<int>(threadIdx.x);
     double t = 0.0;
     if (k < 9) {
-        const double* sums = measure_sums(e) + static_cast<size_t>(blockIdx.x) * slices * 9 + k;
+        const double* sums =
+            measure_sums(e, static_cast<int>(blockIdx.x) / e.n_temps, static_cast<int>(blockIdx.x) % e.n_temps, n_tiles) + k;
 #pragma unroll 16  // (loads in flight)
         for (int g = 0; g < slices; ++g) t += sums[g * 9];
         e.Q[static_cast<size_t>(blockIdx.x) * 9 + k] = t;
@@ -560,14 +563,14 @@ hipError_t launch_anneal_decide(const hsg_ensemble& e, int parity, hipStream_t s
 // size depends on L alone, so a sample range measured on its own sums in the same order.
 constexpr int kMeasureThreadsLarge = 512;
 
-// Slices of a pair of replicas beyond L = 32, by L alone (as above), where the scratch is
-// given: a workgroup reads the pair at the 60 GB/s one CU takes in, so the few workgroups
-// there are leave the memory idle (L = 64, 2 x 9 of them, 113 MB: 107 us, in 32 slices 26 + 5).  At L <= 32 a
-// second launch costs about what slices save.
-static int measure_slices(const hsg_ensemble& e) {
-    const int N = e.L * e.L * e.L;
-    const bool scratch = e.scratch && reinterpret_cast<uintptr_t>(e.scratch) % 256 == 0;
-    return e.L > 32 && scratch && e.n_chains >= 2 && e.Q ? N / 8192 : 1;
+// Slices of a pair of replicas beyond L = 32, by L alone (as above), where the measurement
+// finishes a streaming sweep, whose scratch has room for their sums: a workgroup reads the
+// pair at the 60 GB/s one CU takes in, so the few workgroups there are leave the memory idle
+// (L = 64, 2 x 9 of them, 113 MB: 107 us, in 32 slices 26 + 5).  At L <= 32 a second launch
+// costs about what slices save.
+static int measure_slices(const hsg_ensemble& e, int n_tiles) {
+    const int slices = e.L * e.L * e.L / 8192;
+    return e.L > 32 && e.n_chains >= 2 && e.Q && n_tiles + 9 * slices <= scratch_layout(e).max_tiles ? slices : 1;
 }
 
 template <bool FIN>
@@ -575,19 +578,22 @@ static hipError_t go_measure(const hsg_ensemble& e, int n_tiles, int ctr_add, hi
     const int pairs = e.n_samples * e.n_temps;
     const auto go = [&](auto kern, int nt, int slices) {
         hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(pairs) * slices), dim3(nt), 0, st, e, n_tiles, ctr_add, slices);
-        if (slices > 1) hipLaunchKernelGGL(k_measure_sum, dim3(pairs), dim3(64), 0, st, e, slices);
+        if (slices > 1) hipLaunchKernelGGL(k_measure_sum, dim3(pairs), dim3(64), 0, st, e, n_tiles, slices);
         return hipGetLastError();
     };
     const bool f64 = e.precision == HSG_FP64;
     constexpr int NT = kMeasureThreadsLarge;
-    if (const int n = measure_slices(e); n > 1)
-        return f64 ? go(k_measure<double, NT, FIN, true>, NT, n) : go(k_measure<float, NT, FIN, true>, NT, n);
+    if constexpr (FIN) {
+        if (const int n = measure_slices(e, n_tiles); n > 1)
+            return f64 ? go(k_measure<double, NT, true, true>, NT, n) : go(k_measure<float, NT, true, true>, NT, n);
+    }
     if (e.L > 16) return f64 ? go(k_measure<double, NT, FIN, false>, NT, 1) : go(k_measure<float, NT, FIN, false>, NT, 1);
     // one (sample, temperature) per 128-thread workgroup: 1536 of them at L = 16, 64 x 24
     // (measured 26.4 us per pass against 27.3 with 256 threads and 28.1 with 512)
     return f64 ? go(k_measure<double, 128, FIN, false>, 128, 1) : go(k_measure<float, 128, FIN, false>, 128, 1);
 }
 
+// Neither reads nor writes the scratch, which need not be given.
 hipError_t launch_measure(const hsg_ensemble& e, hipStream_t st) { return go_measure<false>(e, 0, 0, st); }
 
 hipError_t launch_measure_fin(const hsg_ensemble& e, int n_tiles, int ctr_add, hipStream_t st) {
