@@ -230,7 +230,9 @@ hsg_status hsg_anneal_swap(const hsg_ensemble* ens, int n_ens, int parity, int n
  * by heat-bath at beta_{i+1} and beta_i, and their energies recomputed;
  * otherwise nothing changes.  Advances swap_ctr, updates swap_stats and round
  * trips.  If work is not NULL it receives, per pair, ln A and D_i
- * ([S][C][R-1][2]; 0 and -1 for pairs not attempted).  n_temps <= 65536. */
+ * ([S][C][R-1][2]; 0 and -1 for pairs not attempted).  n_temps <= 65536.  All pairs at
+ * L > 16 run faster with a scratch (hsg_scratch_bytes, 256-byte aligned, overwritten);
+ * without one, or with one not so aligned, the same pass runs in one workgroup per chain. */
 hsg_status hsg_decimate_swap(const hsg_ensemble* ens, int n_ens, int pairing, void* stream);
 
 /* Cooling / heating replica exchange (paper Sec. III.B) of the selected pairs of

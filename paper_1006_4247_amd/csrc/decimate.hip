@@ -1169,11 +1169,17 @@ static hipError_t go_decimate(const hsg_ensemble& e, int pairing, int blocks, hi
     }
 }
 
+// The scratch is optional in this call: one that is not given, or not aligned as its regions
+// have to be, is left alone (k_decimate needs none).
+static bool has_scratch(const hsg_ensemble& e) {
+    return e.scratch != nullptr && reinterpret_cast<uintptr_t>(e.scratch) % 256 == 0;
+}
+
 // Workgroups per chain for the split ascending pass (L > 16, scratch given): enough
 // to give the whole launch about 512 workgroups, at least 512 sites of D per
 // workgroup, within the scratch's partial area; 1 = use k_decimate.
 static int split_groups(const hsg_ensemble& e) {
-    if (e.L <= 16 || e.scratch == nullptr) return 1;
+    if (e.L <= 16 || !has_scratch(e)) return 1;
     const int chains = e.n_samples * e.n_chains;
     const long long NH = static_cast<long long>(e.L) * e.L * e.L / 2;
     const ScratchLayout sl = scratch_layout(e);
@@ -1193,7 +1199,7 @@ static int split_groups(const hsg_ensemble& e) {
 // 285 / 155; binary64 L = 18, 16 chains (46 656 sites) 472 / 252 and 414 / 249, L = 24, 16
 // chains 391 / 260 and 252 / 262.  (At L = 28, 8 chains: 471 / 309 and 280 / 299.)
 static int pair_groups(const hsg_ensemble& e) {
-    if (e.L <= 16 || e.scratch == nullptr) return 0;
+    if (e.L <= 16 || !has_scratch(e)) return 0;
     const long long chains = static_cast<long long>(e.n_samples) * e.n_chains;
     const long long NH = static_cast<long long>(e.L) * e.L * e.L / 2;
     if (chains * NH > (e.precision == HSG_FP64 ? 1 << 16 : 1 << 17)) return 0;

@@ -29,3 +29,21 @@ def test_measure_leaves_the_scratch(prec, L, C):
     Q0, chi0, _ = e.measure()
     torch.cuda.synchronize()
     assert torch.equal(Q, Q0) and torch.equal(chi, chi0)
+
+
+@pytest.mark.parametrize("L,S", [(18, 2), (20, 40)])  # one launch per pair; two
+def test_decimate_leaves_a_misaligned_scratch(L, S):
+    """All pairs with a scratch 16 bytes past its alignment: the pass without one, in binary64
+    against the oracle at the tolerances of the other exchange tests."""
+    gpu, ref = make_pair(L, S, 1, hsgref.geometric_betas(1.0, 1.1, 4), SEED + L, prec="fp64")
+    before = _mark(gpu)
+    gpu.desc.scratch = gpu.scratch.data_ptr() + 16
+    w = gpu.decimate_swap(0)
+    lnA, role = ref.decimate_swap(0)
+    torch.cuda.synchronize()
+    assert torch.equal(gpu.scratch, before)
+    assert np.max(np.abs(w.cpu().numpy()[..., 0] - lnA)) <= 1e-10 * max(1.0, np.abs(lnA).max())
+    st = compare_ints(gpu, ref, "misaligned scratch L=%d" % L)
+    assert np.max(np.abs(st["spins"] - ref.spins)) <= 1e-12
+    assert np.max(np.abs(st["energy"] - ref.energy)) <= 1e-9
+    gpu.check()
