@@ -1051,11 +1051,11 @@ static hipError_t coolheat_round(const hsg_ensemble& e, const ChEps& ce, int i0,
 
 // ---------------------------------------------------------------- split ascending pass
 // For L > 16 with few chains.  No pair before i touches the configuration at beta_{i+1},
-// so every pair's heating leg is taken first, at once, in two launches (k_ch_heat: parity
-// 1, then parity 0), GH workgroups per leg.  What is left in order are the cooling legs:
-// two launches per pair over G workgroups per chain, each owning a slice of the sites:
-// k_ch_cool_a decides pair i - 1 (every workgroup alike, its first wave from the sums)
-// and maps parity 0, k_ch_cool_b parity 1.  A configuration stays where it is: the map
+// so every pair's heating leg is taken first, at once, in two launches (k_ch_first: parity
+// 1, then parity 0, and the first pair's cooling leg beside them), GH workgroups per leg.
+// What is left in order are the cooling legs (k_ch_cool): two launches per pair over G
+// workgroups per chain, each owning a slice of the sites: the first decides pair i - 1 (every
+// workgroup alike, its first wave from the sums) and maps parity 0, the second parity 1.  A configuration stays where it is: the map
 // reads it in the slot's spins or in the slot's candidate and writes the other of the two,
 // which an accepted pair makes the configuration; so no launch copies, and k_ch_settle
 // decides the last pair and copies, once per slot, what ended in a candidate.
@@ -1237,12 +1237,10 @@ __device__ __forceinline__ int ch_slice(int NH, int g, int n) {
     return static_cast<int>(static_cast<long long>(NH) * g / n);
 }
 
-// Workgroup (chain, pair, slice g) of the heating legs' first (STEP 0) or second half.
+// Workgroup b, (chain, pair, slice g), of the heating legs' first (STEP 0) or second half.
 template <typename T, int STEP>
-__global__ void __launch_bounds__(kChThreads) k_ch_heat(hsg_ensemble e, ChEps ce, ChGroups gr) {
-    __shared__ double red[kChThreads / 64];
+__device__ __forceinline__ void ch_heat_block(const hsg_ensemble& e, const ChEps& ce, ChGroups gr, int b, double* red) {
     const int L = e.L, N = L * L * L, NH = N / 2, R = e.n_temps;
-    const int b = xcd_order(static_cast<int>(blockIdx.x), static_cast<int>(gridDim.x));
     const int g = b % gr.GH, i = b / gr.GH % (R - 1), ch = b / (gr.GH * (R - 1));
     const T eps = ch_eps<T>(ce, i);
     const ChHeat c = ch_heat(e, ch, gr, i);
@@ -1277,14 +1275,12 @@ __global__ void __launch_bounds__(kChThreads) k_ch_heat(hsg_ensemble e, ChEps ce
     }
 }
 
-// Workgroup (chain, slice g) of pair i's cooling leg, parity 0.
+// Workgroup b, (chain, slice g), of pair i's cooling leg, parity 0.
 template <typename T>
-__global__ void __launch_bounds__(kChThreads) k_ch_cool_a(hsg_ensemble e, ChEps ce, int i, ChGroups gr) {
-    __shared__ double red[kChThreads / 64];
-    __shared__ ChDecision s_dec;
+__device__ __forceinline__ void ch_cool_a_block(const hsg_ensemble& e, const ChEps& ce, int i, ChGroups gr, int b,
+                                                double* red, ChDecision& s_dec) {
     const T eps = ch_eps<T>(ce, i);
     const int L = e.L, N = L * L * L, NH = N / 2, R = e.n_temps;
-    const int b = xcd_order(static_cast<int>(blockIdx.x), static_cast<int>(gridDim.x));  // a chain's slices on one XCD
     const int g = b % gr.G, ch = b / gr.G;
     const ChCool c = ch_cool(e, ch, gr, i);
     const ScratchLayout sl = scratch_layout(e);
@@ -1333,11 +1329,10 @@ __global__ void __launch_bounds__(kChThreads) k_ch_cool_a(hsg_ensemble e, ChEps 
 
 // ... and parity 1.
 template <typename T>
-__global__ void __launch_bounds__(kChThreads) k_ch_cool_b(hsg_ensemble e, ChEps ce, int i, ChGroups gr) {
-    __shared__ double red[kChThreads / 64];
+__device__ __forceinline__ void ch_cool_b_block(const hsg_ensemble& e, const ChEps& ce, int i, ChGroups gr, int b,
+                                                double* red) {
     const T eps = ch_eps<T>(ce, i);
     const int L = e.L, N = L * L * L, NH = N / 2, R = e.n_temps;
-    const int b = xcd_order(static_cast<int>(blockIdx.x), static_cast<int>(gridDim.x));  // a chain's slices on one XCD
     const int g = b % gr.G, ch = b / gr.G;
     const ChCool c = ch_cool(e, ch, gr, i);
     const ScratchLayout sl = scratch_layout(e);
@@ -1357,6 +1352,34 @@ __global__ void __launch_bounds__(kChThreads) k_ch_cool_b(hsg_ensemble e, ChEps 
         c.ld[g] = ld_before + LD;
         c.hs[g] = EN;
     }
+}
+
+// A half (STEP) of all heating legs, and beside it, in the launch's first workgroups, the one
+// of the first pair's cooling leg, which waits for nothing either: a launch less per half
+// counts in a ladder of a few temperatures.
+template <typename T, int STEP>
+__global__ void __launch_bounds__(kChThreads) k_ch_first(hsg_ensemble e, ChEps ce, ChGroups gr, int n_cool) {
+    __shared__ double red[kChThreads / 64];
+    __shared__ ChDecision s_dec;
+    const int b = static_cast<int>(blockIdx.x);
+    if (b >= n_cool)  // uniform over the workgroup
+        ch_heat_block<T, STEP>(e, ce, gr, xcd_order(b - n_cool, static_cast<int>(gridDim.x) - n_cool), red);
+    else if constexpr (STEP == 0)
+        ch_cool_a_block<T>(e, ce, 0, gr, xcd_order(b, n_cool), red, s_dec);
+    else
+        ch_cool_b_block<T>(e, ce, 0, gr, xcd_order(b, n_cool), red);
+}
+
+// A half of the cooling leg of pair i > 0 of every chain, a chain's slices on one XCD.
+template <typename T, int STEP>
+__global__ void __launch_bounds__(kChThreads) k_ch_cool(hsg_ensemble e, ChEps ce, int i, ChGroups gr) {
+    __shared__ double red[kChThreads / 64];
+    __shared__ ChDecision s_dec;
+    const int b = xcd_order(static_cast<int>(blockIdx.x), static_cast<int>(gridDim.x));
+    if constexpr (STEP == 0)
+        ch_cool_a_block<T>(e, ce, i, gr, b, red, s_dec);
+    else
+        ch_cool_b_block<T>(e, ce, i, gr, b, red);
 }
 
 // The last pair's decision and commit; candidates that became configurations over their
@@ -1391,8 +1414,8 @@ __global__ void __launch_bounds__(kChThreads) k_ch_settle(hsg_ensemble e, ChGrou
 }
 
 // Workgroups per leg for the split pass (L > 16): cooling about 512 per launch, a site per
-// thread at least; heating up to eight of 2048 sites; both within the scratch's partial
-// area.  G = 1: not split.
+// thread at least; heating up to eight of 2048 sites, or, where the legs are few, about 512
+// per launch as well; both within the scratch's partial area.  G = 1: not split.
 static ChGroups ch_split_groups(const hsg_ensemble& e) {
     if (e.L <= 16) return {1, 1};
     const int chains = e.n_samples * e.n_chains, R = e.n_temps;
@@ -1401,7 +1424,11 @@ static ChGroups ch_split_groups(const hsg_ensemble& e) {
     const long long per_chain = static_cast<long long>(R) * sl.max_tiles;  // doubles
     if (chains >= 256) return {1, 1};
     ChGroups gr;
+    const long long legs = static_cast<long long>(chains) * (R - 1);
+    const int fill = static_cast<int>((512 + legs - 1) / legs);
+    const int most = NH / kChThreads < kChSlices ? NH / kChThreads : kChSlices;
     gr.GH = NH / 2048 < 1 ? 1 : NH / 2048 < 8 ? NH / 2048 : 8;
+    if (gr.GH < fill) gr.GH = fill < most ? fill : most;
     while (gr.GH > 1 && 2 * static_cast<long long>(R - 1) * (2 * gr.GH + 3) > per_chain) --gr.GH;
     long long G = (512 + chains - 1) / chains;
     const long long room = ((per_chain - static_cast<long long>(R - 1) * (2 * gr.GH + 3)) / 2 - 2) / 2;
@@ -1415,12 +1442,13 @@ static ChGroups ch_split_groups(const hsg_ensemble& e) {
 template <typename T>
 static hipError_t coolheat_split_pass(const hsg_ensemble& e, const ChEps& ce, ChGroups gr, hipStream_t st) {
     const int chains = e.n_samples * e.n_chains, R = e.n_temps;
-    const dim3 heat(static_cast<unsigned>(chains) * (R - 1) * gr.GH), cool(chains * gr.G), nt(kChThreads);
-    hipLaunchKernelGGL((k_ch_heat<T, 0>), heat, nt, 0, st, e, ce, gr);
-    hipLaunchKernelGGL((k_ch_heat<T, 1>), heat, nt, 0, st, e, ce, gr);
-    for (int i = 0; i < R - 1; ++i) {
-        hipLaunchKernelGGL(k_ch_cool_a<T>, cool, nt, 0, st, e, ce, i, gr);
-        hipLaunchKernelGGL(k_ch_cool_b<T>, cool, nt, 0, st, e, ce, i, gr);
+    const dim3 cool(chains * gr.G), first(cool.x + static_cast<unsigned>(chains) * (R - 1) * gr.GH), nt(kChThreads);
+    const int n_cool = static_cast<int>(cool.x);
+    hipLaunchKernelGGL((k_ch_first<T, 0>), first, nt, 0, st, e, ce, gr, n_cool);
+    hipLaunchKernelGGL((k_ch_first<T, 1>), first, nt, 0, st, e, ce, gr, n_cool);
+    for (int i = 1; i < R - 1; ++i) {
+        hipLaunchKernelGGL((k_ch_cool<T, 0>), cool, nt, 0, st, e, ce, i, gr);
+        hipLaunchKernelGGL((k_ch_cool<T, 1>), cool, nt, 0, st, e, ce, i, gr);
         const hipError_t err = hipGetLastError();
         if (err != hipSuccess) return err;
     }
