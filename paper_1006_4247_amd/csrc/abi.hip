@@ -97,11 +97,11 @@ hipStream_t as_stream(void* s) { return static_cast<hipStream_t>(s); }
 // the faster one for the call and no launch shape is asked for, else 3 if a replica fits
 // in LDS, else 2.
 constexpr int kColumn = 100;
-int sweep_path(const hsg_ensemble& e, const hsg_tuning* t, int n_sweeps, int n_hb, int n_or) {
+int sweep_path(const hsg_ensemble& e, const hsg_tuning* t, int n_sweeps, int n_hb, int n_or, bool fused = false) {
     const int path = t ? t->path : 0;
     if (path != 0) return path;
     const bool shaped = t && (t->block_threads != 0 || t->replicas_per_block != 0);
-    if (!shaped && hsg::column_faster(e, n_sweeps, n_hb, n_or)) return kColumn;
+    if (!shaped && hsg::column_faster(e, n_sweeps, n_hb, n_or, fused)) return kColumn;
     if (hsg::resident_supported(e)) return 3;
     return 2;
 }
@@ -409,7 +409,8 @@ hsg_status hsg_sweep_measure(const hsg_ensemble* ens, int n_ens, int n_sweeps, i
             if (err != hipSuccess) return device(err, "sweep and measure");
             continue;
         }
-        if (n_sweeps > 0 && sweep_path(ens[i], nullptr, n_sweeps, n_hb, n_or) == 2) {
+        const int path = sweep_path(ens[i], nullptr, n_sweeps, n_hb, n_or, true);
+        if (n_sweeps > 0 && path == 2) {
             // streaming sweeps: the measurement adds up the last sweep's per-tile
             // energies itself, in place of the sweep's own finishing pass
             int n_tiles = 0;
@@ -420,7 +421,10 @@ hsg_status hsg_sweep_measure(const hsg_ensemble* ens, int n_ens, int n_sweeps, i
             if (err != hipSuccess) return device(err, "measure");
             continue;
         }
-        if (n_sweeps > 0) {
+        if (n_sweeps > 0 && path == kColumn) {
+            err = hsg::launch_column_sweeps(launch_copy(ens[i]), n_sweeps, n_hb, n_or, as_stream(stream));
+            if (err != hipSuccess) return device(err, "sweep");
+        } else if (n_sweeps > 0) {
             s = hsg_sweep(&ens[i], 1, n_sweeps, n_hb, n_or, stream);
             if (s != HSG_OK) return s;
         }

@@ -60,7 +60,8 @@ hipError_t launch_resident_pair(const hsg_ensemble& e, int n_sweeps, int n_hb, i
 // Register-resident sweeps and annealing legs (sweep_column.hip): one workgroup per
 // replica (or leg), whose spins stay in its threads' registers for the whole call.
 bool column_supported(const hsg_ensemble& e);
-bool column_faster(const hsg_ensemble& e, int n_sweeps, int n_hb, int n_or);  // ... and the better kernel for the call
+// ... and the better kernel for the call (fused: with the measurement behind it)
+bool column_faster(const hsg_ensemble& e, int n_sweeps, int n_hb, int n_or, bool fused);
 hipError_t launch_column_sweeps(const hsg_ensemble& e, int n_sweeps, int n_hb, int n_or, hipStream_t st);
 hipError_t launch_column_legs(const hsg_ensemble& e, int parity, int n_hb, int n_or, hipStream_t st);
 

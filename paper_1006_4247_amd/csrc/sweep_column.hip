@@ -35,6 +35,7 @@
 #include "hsg_device.h"
 #include "hsg_launch.h"
 
+#include <cmath>
 #include <type_traits>
 #include <utility>
 
@@ -729,26 +730,61 @@ bool column_supported(const hsg_ensemble& e) {
     return e.L >= 18 && e.L <= 32 && (e.L & 1) == 0;
 }
 
-// ... and where it was measured faster than the streaming kernels.  Those pay per
-// half-sweep, with a launch and at the rate of HBM once the replicas fill it; this one pays
-// once for bringing a replica in and out, and its time hardly depends on the replicas up to
-// one per CU.  So at the larger sizes it takes a few lattice sweeps to win, and for whole
-// columns enough replicas too.  Column / streaming in us at 10, 54, 128 and 432 replicas:
-// binary32 L = 24, 1 + 1 lattice sweeps 38 / 27, 39 / 43, - , 100 / 97; 1 + 3: 49 / 43,
-// 48 / 78, 52 / 78, 106 / 183; 1 + 30: 200 / 296, 202 / 547, 207 / 539, 419 / 1354.
-// L = 28, 1 + 3: 52 / 51, 90 / 84, 93 / 122, 194 / 302; 1 + 30: 437 / 339, 438 / 583,
-// 439 / 856, 888 / 2157.  L = 32, 1 + 3: - , 105 / 77, 111 / 137, 237 / 375; 1 + 30:
-// 507 / 299, 505 / 529, 507 / 979, 1035 / 2713.  Binary64 L = 18, 1 + 1: 44 / 36, 46 / 52,
-// - , 98 / 117; 1 + 30: 161 / 456, 165 / 642, 170 / 550, 347 / 1509.
-bool column_faster(const hsg_ensemble& e, int n_sweeps, int n_hb, int n_or) {
+// ... and where it is the faster kernel.  The streaming kernels pay per half-sweep, with a
+// launch and, once the replicas fill it, at the rate of HBM; this one pays once for bringing a
+// replica in and out, then per lattice sweep, a heat-bath one two to four times an
+// overrelaxation (more from L = 26, where the uniforms have no room in LDS), and its time
+// hardly depends on the replicas up to one per CU.  So it loses few replicas, few lattice
+// sweeps and many heat-baths.  Both times in us from fits to 2385 measured calls, 4 .. 432
+// slots and 1 .. 124 lattice sweeps in 20 compositions: the rule takes the slower kernel by
+// more than 3 % in 8 of them on this side and 35 on the other, all near the line (the worst
+// 44 / 39 us and 41 / 34).  Column / streaming in us at 32, 96, 256 and 432 slots: binary32
+// L = 18, 1 + 0: 14 / 12, 15 / 17, 17 / 23, 23 / 31; L = 22, 1 + 0: 21 / 16, 22 / 21, 24 / 34,
+// 46 / 48; L = 24, 1 + 3: 45 / 42, 46 / 66, 56 / 127, 102 / 182, 1 + 30: 202 / 289, 202 / 474,
+// 212 / 933, 413 / 1344; L = 26, 1 + 3: 68 / 55, 76 / 83, 90 / 165, 167 / 250, 1 + 30: 291 /
+// 362, 300 / 573, 316 / 1229, 619 / 1864; L = 32, 1 + 3: 103 / 54, 105 / 108, 119 / 223, 226 /
+// 362, 1 + 30: 499 / 380, 499 / 795, 518 / 1664, 1027 / 2679; binary64 L = 18, 1 + 3: 48 / 50,
+// 49 / 76, 56 / 131, 105 / 209.  Binary64 L = 16 against the LDS-resident kernel, 6 .. 432
+// slots: 1 + 0 22 / 24 .. 46 / 61, 1 + 30 106 / 148 .. 217 / 305.
+struct ColumnCost {
+    float in_out, per_slot, hb, over;             // this kernel, a round of 256 replicas
+    float sweep, half_min, half_0, half_slot;     // streaming: per sweep, per lattice sweep
+};
+static ColumnCost column_cost(const hsg_ensemble& e) {
+    if (e.precision == HSG_FP64) return {11.4f, 0.031f, 23.9f, 4.1f, 3.8f, 12.8f, 7.5f, 0.091f};
+    switch (e.L) {
+        case 18: return {6.5f, 0.012f, 7.6f, 3.0f, 4.0f, 8.9f, 7.7f, 0.039f};
+        case 20: return {6.4f, 0.013f, 8.3f, 3.1f, 3.4f, 8.7f, 6.9f, 0.056f};
+        case 22: return {8.6f, 0.016f, 12.5f, 4.2f, 4.7f, 9.2f, 7.6f, 0.077f};
+        case 24: return {9.6f, 0.034f, 15.7f, 5.9f, 5.0f, 8.8f, 6.6f, 0.089f};
+        case 26: return {11.5f, 0.063f, 26.1f, 8.8f, 7.0f, 8.1f, 8.0f, 0.121f};
+        case 28: return {10.1f, 0.042f, 38.5f, 12.8f, 7.0f, 8.6f, 7.6f, 0.143f};
+        case 30: return {10.8f, 0.053f, 44.1f, 15.2f, 7.4f, 8.8f, 8.2f, 0.179f};
+        default: return {11.7f, 0.063f, 44.3f, 14.8f, 6.5f, 8.3f, 6.1f, 0.189f};
+    }
+}
+
+// fused: the streaming sweeps' last finishing launch is the measurement's (launch_measure_fin).
+bool column_faster(const hsg_ensemble& e, int n_sweeps, int n_hb, int n_or, bool fused) {
     if (!column_supported(e)) return false;
-    const bool small = e.precision == HSG_FP64 ? e.L == 16 : e.L <= 22;
-    if (small) return true;
-    const long long lattice_sweeps = static_cast<long long>(n_sweeps) * (n_hb + n_or);
-    const long long slots = static_cast<long long>(e.n_samples) * e.n_chains * e.n_temps;
-    if (e.L <= 26) return lattice_sweeps >= (slots < 32 ? 8 : 4);
+    const bool f64 = e.precision == HSG_FP64;
+    if (f64 && e.L == 16) return true;
     // (whole columns neither renormalise nor take the energy after a heat-bath)
-    return n_hb > 0 && n_or > 0 && slots >= 48 && lattice_sweeps >= (slots < 96 ? 20 : 4);
+    if (e.L > 26 && (n_hb == 0 || n_or == 0)) return false;
+    const ColumnCost c = column_cost(e);
+    const float n = static_cast<float>(n_sweeps), slots = static_cast<float>(e.n_samples) * e.n_chains * e.n_temps;
+    const float once = c.in_out + n * (n_hb * c.hb + n_or * c.over);
+    float column;
+    if (!f64 && e.L == 18)  // two replicas per CU
+        column = (once + c.per_slot * std::fmin(slots, 256.0f)) * std::fmax(1.0f, std::ceil(slots / 256.0f) * 0.75f);
+    else
+        column = once * std::ceil(slots / 256.0f) + c.per_slot * slots;
+    // (workgroups in a number that is no multiple of the XCDs are not ordered by them: xcd_order)
+    const long long tiles = (static_cast<long long>(e.L) * e.L * e.L / 4 + 255) / 256;
+    const bool ordered = tiles * e.n_samples * e.n_chains * e.n_temps % 8 == 0;
+    const float half = std::fmax(c.half_min, c.half_0 + c.half_slot * slots * (ordered ? 1.0f : 1.5f));
+    const float stream = n * (c.sweep + (n_hb * (f64 ? 1.3f : 1.05f) + n_or) * half) - (fused ? c.sweep : 0.0f);
+    return column <= (!f64 && e.L <= 22 ? 1.0f : 0.97f) * stream;
 }
 
 hipError_t launch_column_sweeps(const hsg_ensemble& e, int n_sweeps, int n_hb, int n_or, hipStream_t st) {

@@ -30,9 +30,9 @@ def _same(a, b):
 
 # the energy taken in an overrelaxation, a renormalising and a heat-bath half-sweep
 @pytest.mark.parametrize("prec,L", SIZES)
-@pytest.mark.parametrize("n,n_hb,n_or", [(2, 1, 10), (2, 0, 8), (8, 1, 0)])
-def test_energy_bits(prec, L, n, n_hb, n_or):
-    a, b = _ensemble(prec, L, 2, 3, 6), _ensemble(prec, L, 2, 3, 6)
+@pytest.mark.parametrize("S,n,n_hb,n_or", [(2, 2, 1, 10), (2, 2, 0, 8), (10, 4, 1, 0)])
+def test_energy_bits(prec, L, S, n, n_hb, n_or):
+    a, b = _ensemble(prec, L, S, 4, 6), _ensemble(prec, L, S, 4, 6)
     a.sweep(n, n_hb, n_or)
     b.sweep(n, n_hb, n_or, tuning={"path": 2})
     _same(a, b)
