@@ -177,8 +177,8 @@ __device__ __forceinline__ T ch_eps(const ChEps& c, int i) {
     return static_cast<T>(c.pair ? c.pair[i] : c.eps);
 }
 
-// LDS-resident legs (L <= 16) of one pair per chain: the replica in LDS, couplings from
-// global memory.
+// LDS-resident legs (L <= 16) of one pair per chain, or of few pairs: the replica in LDS,
+// couplings from global memory.
 //
 // PREV (ascending rounds i0 >= 1, one pair per chain): the cooling leg's workgroup
 // first decides pair i0 - 1 of its chain and copies that pair's accepted candidates
@@ -934,13 +934,13 @@ static hipError_t go_leg_nt(const hsg_ensemble& e, const ChEps& ce, int i0, int 
 template <typename T, int L>
 static hipError_t go_leg_res(const hsg_ensemble& e, const ChEps& ce, int i0, int istep, int npc, int blocks, bool prev,
                              hipStream_t st) {
-    // one pair per chain: binary32 legs with 1024 threads, binary64 with 512 (its site
+    // few pairs per launch: binary32 legs with 1024 threads, binary64 with 512 (its site
     // maps need more than the 128 registers a thread of a 1024-thread workgroup gets)
     constexpr int NH = L * L * L / 2;
     constexpr int NTMAX = sizeof(T) == 4 ? 1024 : 512;
     constexpr int NT1 = NH >= NTMAX ? NTMAX : ((NH + 63) / 64) * 64;
     constexpr int NTS = NT1 > kChThreads ? NT1 : kChThreads;
-    if (npc != 1) return hipErrorInvalidValue;  // (k_coolheat_pair)
+    if (prev && npc != 1) return hipErrorInvalidValue;
     if (prev) return go_leg_nt<T, L, NTS, true>(e, ce, i0, istep, npc, blocks, st);
     return go_leg_nt<T, L, NTS, false>(e, ce, i0, istep, npc, blocks, st);
 }
@@ -1022,9 +1022,16 @@ static hipError_t coolheat_round(const hsg_ensemble& e, const ChEps& ce, int i0,
     const int n_chains = e.n_samples * e.n_chains;
     hipError_t err = hipSuccess;
     // even or odd pairs at L = 4 .. 16: both legs in one workgroup, but for a single pair per
-    // chain, whose legs are sooner done side by side (binary32 L = 16, 16 chains x 3
-    // temperatures: 18.4 against 21.4 us; binary64 90 against 107)
-    if (e.L >= 4 && e.L <= 16 && npc > 1)
+    // chain and for pairs so few that their legs are sooner done side by side, the decision
+    // and the copies in launches of their own: in binary64 while the legs have a CU each, in
+    // binary32, where those launches weigh more, up to a quarter of the CUs.  Side by side /
+    // in one workgroup, us a call at 4, 64 and 96 pairs: binary32 L = 10 12.2 / 13.8, 13.1 /
+    // 13.9, 14.7 / 14.4; L = 16 15.4 / 19.4, 18.5 / 19.8, 21.9 / 20.5 (L = 8 12.2 / 9.6, 13.1 /
+    // 10.4, 13.3 / 10.5); binary64 at 64, 128 and 144 pairs: L = 4 54 / 58, 56 / 58, 59 / 60;
+    // L = 10 98 / 138, 95 / 128, 134 / 124; L = 16 209 / 228, 241 / 283, 417 / 281.
+    const long long pairs = static_cast<long long>(n_chains) * npc;
+    const bool few = e.precision == HSG_FP64 ? pairs <= 128 : e.L >= 10 && pairs <= 64;
+    if (e.L >= 4 && e.L <= 16 && npc > 1 && !few)
         return e.precision == HSG_FP64 ? go_pairs<double>(e, ce, i0, npc, st) : go_pairs<float>(e, ce, i0, npc, st);
     if (npc > 0) {
         err = e.precision == HSG_FP64 ? go_legs<double>(e, ce, i0, istep, npc, false, st)
