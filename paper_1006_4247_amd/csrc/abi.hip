@@ -310,7 +310,7 @@ hsg_status hsg_anneal_swap(const hsg_ensemble* ens, int n_ens, int parity, int n
     for (int i = 0; i < n_ens; ++i) {
         hipError_t err;
         const hsg_ensemble e = launch_copy(ens[i]);
-        if (hsg::column_supported(e) && e.L > 16 && e.L <= 26)
+        if (hsg::column_legs_faster(e, n_hb, n_or))
             err = hsg::launch_column_legs(e, parity, n_hb, n_or, as_stream(stream));
         else if (hsg::resident_supported(e))
             err = hsg::launch_resident(e, 0, n_hb, n_or, 1, parity, 0, as_stream(stream));

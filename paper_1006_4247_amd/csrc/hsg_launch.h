@@ -63,6 +63,7 @@ bool column_supported(const hsg_ensemble& e);
 // ... and the better kernel for the call (fused: with the measurement behind it)
 bool column_faster(const hsg_ensemble& e, int n_sweeps, int n_hb, int n_or, bool fused);
 hipError_t launch_column_sweeps(const hsg_ensemble& e, int n_sweeps, int n_hb, int n_or, hipStream_t st);
+bool column_legs_faster(const hsg_ensemble& e, int n_hb, int n_or);
 hipError_t launch_column_legs(const hsg_ensemble& e, int parity, int n_hb, int n_or, hipStream_t st);
 
 // Wavefront path: one workgroup per replica walking its z-planes, one HBM pass per

@@ -803,16 +803,28 @@ hipError_t launch_column_sweeps(const hsg_ensemble& e, int n_sweeps, int n_hb, i
     }
 }
 
-// (binary64 L = 16 legs run in k_resident_leg)
+// Annealing legs: where this kernel is not the slower one for any number of legs.  The choice
+// does not depend on that number, as the two kernels add the energies of a leg in different
+// orders and its work decides the exchange: a shard of an ensemble has to take the decisions
+// of the whole.  A leg takes its energy in every sweep and holds more than a replica's sweeps
+// do, so few legs with many heat-baths stream sooner.  Column / streaming, us a call, K = 8,
+// 2 and 416 legs: binary32 L = 22, 1 + 0: 151 / 145, 335 / 471, 1 + 3: 257 / 380, 547 / 1424;
+// L = 24, 1 + 1: 266 / 223, 640 / 862 (streams), 1 + 3: 358 / 371, 821 / 1569; L = 26, 1 + 3: 594
+// / 391, 1487 / 2065 (streams); binary64 L = 18, 1 + 0: 382 / 208, 859 / 591 (streams), 1 + 3: 401
+// / 577, 888 / 1732.  (Binary64 L = 16: k_resident_leg.)
+bool column_legs_faster(const hsg_ensemble& e, int n_hb, int n_or) {
+    if (!column_supported(e) || e.L <= 16 || e.L > 24) return false;
+    if (e.precision == HSG_FP32 && e.L <= 22) return true;
+    return n_or >= 2 && n_or >= 3 * n_hb;
+}
+
 hipError_t launch_column_legs(const hsg_ensemble& e, int parity, int n_hb, int n_or, hipStream_t st) {
-    if (e.precision == HSG_FP64)
-        return e.L == 18 ? go_column_legs<double, 18>(e, parity, n_hb, n_or, st) : hipErrorInvalidValue;
+    if (e.precision == HSG_FP64) return go_column_legs<double, 18>(e, parity, n_hb, n_or, st);
     switch (e.L) {
         case 18: return go_column_legs<float, 18>(e, parity, n_hb, n_or, st);
         case 20: return go_column_legs<float, 20>(e, parity, n_hb, n_or, st);
         case 22: return go_column_legs<float, 22>(e, parity, n_hb, n_or, st);
         case 24: return go_column_legs<float, 24>(e, parity, n_hb, n_or, st);
-        case 26: return go_column_legs<float, 26>(e, parity, n_hb, n_or, st);
         default: return hipErrorInvalidValue;
     }
 }
