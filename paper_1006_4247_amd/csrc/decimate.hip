@@ -835,8 +835,8 @@ __global__ void __launch_bounds__(kDecThreads) k_dec_split_apply(hsg_ensemble e,
 // What bounds it: in one launch, three round trips to memory one after the other (the
 // sums, x's configuration, the new sums) and one site's arithmetic; what does not depend
 // on the decision (couplings, y's configuration and draws) does not wait for it.  Binary32
-// L = 24, 8 x 2 chains x 27 temperatures, 1 pair in 3 accepted: 8.4 us a pair, against
-// 16.2 us in two launches; L = 18: 8.0 against 15.5 us.
+// L = 24, 16 chains x 27 temperatures, 1 pair in 3 accepted: 8.5 us a pair, against 16.4 us
+// in two launches; L = 18: 6.7 against 15.7 us.
 //
 // In the scratch's partial area, per chain and pair parity (pair i's record is written
 // while pair i - 1's is read): three sums per slice and the record.
@@ -1192,12 +1192,14 @@ static int split_groups(const hsg_ensemble& e) {
 
 // Workgroups per chain for one launch per pair (L > 16, scratch given): a site of each
 // configuration per thread, 64 at most, within the scratch's partial area (two pairs'
-// records); 0 = not taken.  Drawing before the decision is wasted on a rejected pair, so
-// it is for launches whose sites do not fill the chip: two launches / one, in us a pass,
-// with 1 pair in 3 and with none accepted: binary32 L = 24, 16 chains (110 592 sites) 438 /
-// 228 and 282 / 220, 64 chains 246 / 226 and 167 / 215; L = 18, 16 chains 305 / 161 and
-// 285 / 155; binary64 L = 18, 16 chains (46 656 sites) 472 / 252 and 414 / 249, L = 24, 16
-// chains 391 / 260 and 252 / 262.  (At L = 28, 8 chains: 471 / 309 and 280 / 299.)
+// records); 0 = not taken.  Drawing before the decision is wasted on a rejected pair, so it
+// is for launches whose sites do not fill the chip.  Two launches / one, us a pass of 27
+// temperatures, with 1 pair in 4 and with hardly one accepted, at the most chains that take it
+// and at more: binary32 (2^17 sites) L = 18, 44 chains 475 / 279 and 251 / 269, 64: 470 / 294 and
+// 269 / 284, 88: 488 / 433 and 273 / 424; L = 24, 18: 491 / 239 and 259 / 227, 24: 462 / 278 and 257 /
+// 266, 36: 559 / 374 and 297 / 352; L = 28, 11: 484 / 241 and 269 / 229, 16: 463 / 283 and 265 / 270;
+// binary64 (2^16) L = 18, 22: 653 / 344 and 361 / 336, 44: 662 / 498 and 367 / 487; L = 32, 4: 406 /
+// 246 and 326 / 238, 6: 434 / 354 and 328 / 350.
 static int pair_groups(const hsg_ensemble& e) {
     if (e.L <= 16 || !has_scratch(e)) return 0;
     const long long chains = static_cast<long long>(e.n_samples) * e.n_chains;
