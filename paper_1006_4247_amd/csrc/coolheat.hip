@@ -1257,6 +1257,9 @@ __device__ __forceinline__ void ch_heat_block(const hsg_ensemble& e, const ChEps
     T* cand = reinterpret_cast<T*>(scr + sl.cand) + gs * 3 * N;
     const T* spins = static_cast<const T*>(e.spins) + gs * 3 * N;
     const T* __restrict__ J = static_cast<const T*>(e.couplings) + static_cast<size_t>(ch / e.n_chains) * 3 * N;
+    if (STEP == 0 && g == 0 && i == 0)  // every slot is in its spins (also one that a corrupted label leaves out)
+        for (int r = static_cast<int>(threadIdx.x); r < R; r += kChThreads)
+            reinterpret_cast<int*>(scr + sl.flags)[static_cast<size_t>(ch) * R + r] = 0;
     double en = 0.0;
     const double ld = ch_half<T, true>(J, L, 1 - STEP, ch_slice(NH, g, gr.GH), ch_slice(NH, g + 1, gr.GH), eps, STEP == 1,
                                        &en, [&] { return ChPlaces<T>{STEP ? cand : spins, spins, cand}; });
@@ -1266,14 +1269,11 @@ __device__ __forceinline__ void ch_heat_block(const hsg_ensemble& e, const ChEps
         if constexpr (STEP == 0) {
             c.ld[g] = LD;
             if (g == 0) {
-                int* in_cand = reinterpret_cast<int*>(scr + sl.flags);
                 *c.en = e.energy[gs];
                 *c.slot = static_cast<int>(gs - static_cast<size_t>(ch) * R);
                 const Words w = philox(static_cast<uint32_t>(i), e.swap_ctr[ch], e.chain_base + static_cast<uint32_t>(ch),
                                        kTagSwap << 24, key_lo(e.seed), key_hi(e.seed));
                 *c.logu = log(u01_52(w.w0, w.w1));
-                in_cand[gs] = 0;
-                if (i == 0) in_cand[static_cast<size_t>(ch) * R + label(e.slot_of_temp[ch * R], R, e.guard)] = 0;
             }
         } else {
             c.ld[g] += LD;
