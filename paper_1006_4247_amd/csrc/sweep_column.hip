@@ -532,7 +532,7 @@ struct ColumnLeg {  // an annealing leg's protocol
 // its protocol points, ADJ in adjoint order), to `gd`.  Returns the final energy; W is the
 // leg's work.
 template <typename T, int L, bool LEG, bool ADJ>
-__device__ __forceinline__ double column_run(const hsg_ensemble& e, int slot, const T* __restrict__ gs, T* gd, int n_sweeps,
+__device__ __forceinline__ double column_run(const hsg_ensemble& e, int slot, const T* gs, T* gd, int n_sweeps,
                                              int n_hb, int n_or, const ColumnLeg& leg, double H, double& W,
                                              unsigned char* smem_raw, double* red, double& s_H) {
     using M = Column<T, L>;
@@ -659,6 +659,14 @@ __global__ void __launch_bounds__((Column<T, L>::NT), (Column<T, L>::WPE))
     if (threadIdx.x == 0) e.energy[slot] = H;
 }
 
+// A leg's sweeps, whose source and destination are two arrays (a replica's are one).
+template <typename T, int L, bool ADJ>
+__device__ __forceinline__ double column_leg_run(const hsg_ensemble& e, int slot, const T* __restrict__ gs,
+                                                 T* __restrict__ gd, int n_hb, int n_or, const ColumnLeg& leg, double H,
+                                                 double& W, unsigned char* smem_raw, double* red, double& s_H) {
+    return column_run<T, L, true, ADJ>(e, slot, gs, gd, 0, n_hb, n_or, leg, H, W, smem_raw, red, s_H);
+}
+
 // Annealing legs of the pairs i = parity (mod 2), one workgroup per (chain, pair, leg),
 // from the spins into the candidate buffer.
 template <typename T, int L>
@@ -691,9 +699,9 @@ __global__ void __launch_bounds__((Column<T, L>::NT), (Column<T, L>::WPE))
     if (leg.K == 0)
         W = down ? (leg.a - leg.b) * H : (leg.b - leg.a) * H;
     else if (down)
-        H = column_run<T, L, true, true>(e, slot, gs, gd, 0, n_hb, n_or, leg, H, W, smem_raw, red, s_H);
+        H = column_leg_run<T, L, true>(e, slot, gs, gd, n_hb, n_or, leg, H, W, smem_raw, red, s_H);
     else
-        H = column_run<T, L, true, false>(e, slot, gs, gd, 0, n_hb, n_or, leg, H, W, smem_raw, red, s_H);
+        H = column_leg_run<T, L, false>(e, slot, gs, gd, n_hb, n_or, leg, H, W, smem_raw, red, s_H);
     if (threadIdx.x == 0) {
         e.work[(static_cast<size_t>(ch) * (R - 1) + ipair) * 2 + down] = W;
         reinterpret_cast<double*>(scr + sl.cand_energy)[slot] = H;
