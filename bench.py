@@ -81,16 +81,25 @@ def hbm_bytes_per_launch(w, measure=False):
 
 
 def step_kernel(w, fused_ok=True):
-    """The kernel of the workload's step that sweeps every replica (the step's dominant
-    kernel), as the library picks it: (name, whether it also measures).  With two
-    chains at binary32 L = 16 the sweep and the measurement are one launch, unless
-    the step is asked for unfused (the measurement as a launch of its own)."""
+    """The LDS-resident kernel for the workload's step that sweeps every replica: (name,
+    whether it also measures).  With two chains at binary32 L = 16 the sweep and the
+    measurement are one launch, unless the step is asked for unfused (the measurement as
+    a launch of its own).  See launched_kernel for the sizes whose default sweep is
+    register-resident."""
     if fused_ok and w["prec"] == "fp32" and w["L"] == 16 and w["C"] == 2:
         return "k_resident_mseq<float,16,512>", True
     nq = w["L"] ** 3 // 4
     nt = min(1024, (nq + 63) // 64 * 64)
     nt = 512 if nt >= 1024 else nt
     return "k_resident<%s,%d,%d>" % ("float" if w["prec"] == "fp32" else "double", w["L"], nt), False
+
+
+def launched_kernel(w, fused_ok=True):
+    """The kernel the library launches for that step (the step's dominant kernel), as
+    step_kernel: binary64 L = 16 sweeps are register-resident by default."""
+    if w["prec"] == "fp64" and w["L"] == 16:
+        return "k_column<double,16>", False
+    return step_kernel(w, fused_ok)
 
 
 OPS_OVERLAP_SITE = 9  # the overlap tensor: nine products per site of a (sample, temperature)
@@ -848,9 +857,7 @@ def headline(torch, hsg, w, steps, warmup, clock_warmup_s, fused_ok=True, split=
     ens.stream = None  # eager calls below go to this stream (the run had given it its own)
     # the dominant kernel (the step's sweep, with the measurement where the library
     # fuses it): back-to-back launches on this stream, events around them
-    name, fused = step_kernel(w, fused_ok)
-    if w["prec"] == "fp64" and w["L"] == 16:
-        name = "k_column<double,16>"  # (the register-resident kernel takes these sweeps)
+    name, fused = launched_kernel(w, fused_ok)
 
     def launch():
         if fused:

@@ -145,9 +145,10 @@ class PTRun:
             cur.wait_stream(s)
 
     def kind_groups(self):
-        """Stream groups by kind: the streaming classes (HBM-bound) on stream 0, one after
-        another so that each has the MALL to itself, the LDS-resident classes
-        (compute-bound) beside them on stream 1; None if the batch has one kind only."""
+        """Stream groups by kind: the classes above L = 16 (register-resident or streaming
+        sweeps; the streaming ones are HBM-bound and have the MALL to themselves one after
+        another) on stream 0, the LDS-resident classes beside them on stream 1; None if the
+        batch has one kind only."""
         res = []
         for e, t in zip(self.ens, self.tunings):
             path = (t or {}).get("path", 0)
@@ -159,7 +160,7 @@ class PTRun:
     def _pick_concurrency(self, steps=20):
         """Autotuning of the batch's order: time captured cycles with the size classes one
         after another, with each on its own stream, and (batches of both kinds) with the
-        streaming classes on one stream beside the LDS-resident ones (real steps of the
+        classes above L = 16 on one stream beside the LDS-resident ones (real steps of the
         run, counted), and keep the fastest.  Returns the choice for `concurrent`."""
         import time
         best, best_t = False, None
