@@ -531,8 +531,8 @@ struct ColumnLeg {  // an annealing leg's protocol
 // The sweeps of one replica: from `gs`, through n_sweeps sweeps (LEG: the leg's K sweeps at
 // its protocol points, ADJ in adjoint order), to `gd`.  Returns the final energy; W is the
 // leg's work.
-template <typename T, int L, bool LEG, bool ADJ>
-__device__ __forceinline__ double column_run(const hsg_ensemble& e, int slot, const T* gs, T* gd, int n_sweeps,
+template <typename T, int L, bool LEG, bool ADJ, class Src>
+__device__ __forceinline__ double column_run(const hsg_ensemble& e, int slot, Src gs, T* gd, int n_sweeps,
                                              int n_hb, int n_or, const ColumnLeg& leg, double H, double& W,
                                              unsigned char* smem_raw, double* red, double& s_H) {
     using M = Column<T, L>;
@@ -654,17 +654,9 @@ __global__ void __launch_bounds__((Column<T, L>::NT), (Column<T, L>::WPE))
     const int slot = xcd_order(static_cast<int>(blockIdx.x), static_cast<int>(gridDim.x));
     T* gs = static_cast<T*>(e.spins) + static_cast<size_t>(slot) * 3 * Column<T, L>::N;
     double W = 0.0;
-    const double H = column_run<T, L, false, false>(e, slot, gs, gs, n_sweeps, n_hb, n_or, ColumnLeg{}, 0.0, W, smem_raw,
+    const double H = column_run<T, L, false, false, const T*>(e, slot, gs, gs, n_sweeps, n_hb, n_or, ColumnLeg{}, 0.0, W, smem_raw,
                                                     red, s_H);
     if (threadIdx.x == 0) e.energy[slot] = H;
-}
-
-// A leg's sweeps, whose source and destination are two arrays (a replica's are one).
-template <typename T, int L, bool ADJ>
-__device__ __forceinline__ double column_leg_run(const hsg_ensemble& e, int slot, const T* __restrict__ gs,
-                                                 T* __restrict__ gd, int n_hb, int n_or, const ColumnLeg& leg, double H,
-                                                 double& W, unsigned char* smem_raw, double* red, double& s_H) {
-    return column_run<T, L, true, ADJ>(e, slot, gs, gd, 0, n_hb, n_or, leg, H, W, smem_raw, red, s_H);
 }
 
 // Annealing legs of the pairs i = parity (mod 2), one workgroup per (chain, pair, leg),
@@ -694,14 +686,15 @@ __global__ void __launch_bounds__((Column<T, L>::NT), (Column<T, L>::WPE))
     const ScratchLayout sl = scratch_layout(e);
     unsigned char* scr = static_cast<unsigned char*>(e.scratch);
     double H = e.energy[slot], W = 0.0;
+    using Src = const T* __restrict__;  // (source and destination of a leg are two arrays, a replica's are one)
     const T* gs = static_cast<const T*>(e.spins) + static_cast<size_t>(slot) * 3 * N;
     T* gd = reinterpret_cast<T*>(scr + sl.cand) + static_cast<size_t>(slot) * 3 * N;
     if (leg.K == 0)
         W = down ? (leg.a - leg.b) * H : (leg.b - leg.a) * H;
     else if (down)
-        H = column_leg_run<T, L, true>(e, slot, gs, gd, n_hb, n_or, leg, H, W, smem_raw, red, s_H);
+        H = column_run<T, L, true, true, Src>(e, slot, gs, gd, 0, n_hb, n_or, leg, H, W, smem_raw, red, s_H);
     else
-        H = column_leg_run<T, L, false>(e, slot, gs, gd, n_hb, n_or, leg, H, W, smem_raw, red, s_H);
+        H = column_run<T, L, true, false, Src>(e, slot, gs, gd, 0, n_hb, n_or, leg, H, W, smem_raw, red, s_H);
     if (threadIdx.x == 0) {
         e.work[(static_cast<size_t>(ch) * (R - 1) + ipair) * 2 + down] = W;
         reinterpret_cast<double*>(scr + sl.cand_energy)[slot] = H;
