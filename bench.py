@@ -648,7 +648,7 @@ def uneven_study(torch, hsg, steps, warm=20):
     half-sweep the updated half read and written and the other half read, couplings once
     per sample; wavefront: one read and one write per lattice sweep).  Four forms: the
     library's default kernels with the classes one after another, the same with each
-    class on its own stream, the streaming classes one after another beside the
+    class on its own stream, the classes above L = 16 one after another beside the
     LDS-resident ones, and the autotuner's kernels and order; and, for the sweeps
     alone, one persistent launch over all classes (tuning path 5) against the classes'
     sweeps one after another."""
